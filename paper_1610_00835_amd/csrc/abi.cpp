@@ -167,6 +167,20 @@ ert_status ensure_workspace(ert_plan_impl* p, size_t vec_elems, size_t red_elems
     return ERT_OK;
 }
 
+ert_status ensure_column(ert_plan_impl* p, size_t elems)
+{
+    if (elems <= p->h_col_elems) return ERT_OK;
+    if (p->h_col) (void)hipHostFree(p->h_col);
+    p->h_col = nullptr;
+    p->h_col_elems = 0;
+    if (hipHostMalloc((void**)&p->h_col, elems * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        record_error("ert_vie_solve: page-locked host allocation failed");
+        return ERT_ENOMEM;
+    }
+    p->h_col_elems = elems;
+    return ERT_OK;
+}
+
 ert_status ensure_solve_scratch(ert_plan_impl* p, size_t elems)
 {
     if (elems <= p->solve_elems) return ERT_OK;
@@ -232,16 +246,20 @@ ert_status gmres_run(ert_plan_impl* p, int method, int prec, const double* b, do
     const bool flex = pc && pc->active();
     const int nz = flex ? m : 0;
     // workspace: V (m+1 vectors), Z (m, flexible only), w, r
-    ERT_TRY(ensure_workspace(p, (size_t)(m + nz + 3) * N, (size_t)kPartials * (m + 2) + 4 * (size_t)(m + 2)));
+    ERT_TRY(ensure_workspace(p, (size_t)(m + nz + 3) * N, 2 * (size_t)kPartials * (m + 2) + 4 * (size_t)(m + 2)));
+    ERT_TRY(ensure_column(p, (size_t)m + 2));
     double* V = p->d_ws;
     double* Z = V + (size_t)(m + 1) * N;
     double* w = Z + (size_t)nz * N;
     double* r = w + N;
     double* partial = p->d_red;
-    double* dh = partial + (size_t)kPartials * (m + 2);    // h1 (m+1) then h2 (m+1) then norm
-    double* dh2 = dh + (m + 2);
-    double* dy = dh2 + (m + 2);
-    std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), hh(m + 2);
+    double* partial2 = partial + (size_t)kPartials * (m + 2);
+    double* dh = partial2 + (size_t)kPartials * (m + 2);   // Gram-Schmidt coefficients (m)
+    double* dy = dh + (m + 2);
+    // the triangular factor by columns (column j: rows 0 .. j), grown with the basis
+    std::vector<double> H, cs(m), sn(m), g(m + 1), y(m);
+    auto col = [](int j) { return (size_t)j * (j + 1) / 2; };
+    double* hh = p->h_col;
     ert_status st = ERT_OK;
 
     ERT_TRY(dev_zero(p->stream, u, N));
@@ -263,7 +281,7 @@ ert_status gmres_run(ert_plan_impl* p, int method, int prec, const double* b, do
             hist->count++;
         }
         ERT_TRY(dev_scale(p->stream, V, rsrc, 1.0 / beta, N));
-        std::fill(H.begin(), H.end(), 0.0);
+        H.clear();
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
         int k = 0;
@@ -285,26 +303,20 @@ ert_status gmres_run(ert_plan_impl* p, int method, int prec, const double* b, do
             }
             ERT_TRY(apply_dispatch(p, ERT_OP_A, method, prec, vj, w, 1));
             rs->matvecs++;
-            ERT_TRY(dev_multidot(p->stream, V, N, j + 1, w, N, partial, dh));
-            ERT_TRY(dev_gemv_sub(p->stream, V, N, j + 1, dh, w, N));
-            ERT_TRY(dev_multidot(p->stream, V, N, j + 1, w, N, partial, dh2));
-            ERT_TRY(dev_gemv_sub(p->stream, V, N, j + 1, dh2, w, N));
-            ERT_TRY(dev_small_add(p->stream, dh, dh2, j + 1));
-            ERT_TRY(dev_multidot(p->stream, w, N, 1, w, N, partial, dh + j + 1));
-            ERT_HIP(hipMemcpyAsync(hh.data(), dh, sizeof(double) * (j + 2), hipMemcpyDeviceToHost, p->stream));
+            ERT_TRY(dev_orthogonalise(p->stream, V, N, j + 1, w, N, partial, partial2, dh, p->h_col));
             ERT_HIP(hipStreamSynchronize(p->stream));
             const double hn = std::sqrt(hh[j + 1] > 0.0 ? hh[j + 1] : 0.0);
-            for (int i = 0; i <= j; ++i) H[(size_t)i * m + j] = hh[i];
             for (int i = 0; i < j; ++i) {
-                double a = H[(size_t)i * m + j], c = H[(size_t)(i + 1) * m + j];
-                H[(size_t)i * m + j] = cs[i] * a + sn[i] * c;
-                H[(size_t)(i + 1) * m + j] = -sn[i] * a + cs[i] * c;
+                const double a = hh[i], c = hh[i + 1];
+                hh[i] = cs[i] * a + sn[i] * c;
+                hh[i + 1] = -sn[i] * a + cs[i] * c;
             }
-            double a = H[(size_t)j * m + j];
+            const double a = hh[j];
             double den = std::hypot(a, hn);
             cs[j] = den == 0.0 ? 1.0 : a / den;
             sn[j] = den == 0.0 ? 0.0 : hn / den;
-            H[(size_t)j * m + j] = den;
+            hh[j] = den;
+            H.insert(H.end(), hh, hh + j + 1);
             g[j + 1] = -sn[j] * g[j];
             g[j] = cs[j] * g[j];
             rs->iters++;
@@ -315,10 +327,11 @@ ert_status gmres_run(ert_plan_impl* p, int method, int prec, const double* b, do
         }
         for (int i = k - 1; i >= 0; --i) {
             double s = g[i];
-            for (int c = i + 1; c < k; ++c) s -= H[(size_t)i * m + c] * y[c];
+            for (int c = i + 1; c < k; ++c) s -= H[col(c) + i] * y[c];
             // a zero pivot only arises from a zero search direction (breakdown of a
             // flexible step): that direction takes no weight
-            y[i] = H[(size_t)i * m + i] != 0.0 ? s / H[(size_t)i * m + i] : 0.0;
+            const double d = H[col(i) + i];
+            y[i] = d != 0.0 ? s / d : 0.0;
         }
         ERT_HIP(hipMemcpyAsync(dy, y.data(), sizeof(double) * k, hipMemcpyHostToDevice, p->stream));
         ERT_TRY(dev_gemv_add(p->stream, flex ? Z : V, N, k, dy, u, N));
@@ -515,6 +528,7 @@ void ert_vie_destroy(ert_vie_plan_t p)
     (void)hipFree(p->d_ws);
     (void)hipFree(p->d_red);
     (void)hipFree(p->d_solve);
+    if (p->h_col) (void)hipHostFree(p->h_col);
     delete p;
 }
 

@@ -13,54 +13,140 @@ constexpr int kBlk = 256;
 constexpr int kRedBlocks = 240;   // partial sums per column
 constexpr int kColGroup = 8;      // columns reduced together per pass over w
 
-__device__ __forceinline__ double block_sum(double v, double* sh)
+constexpr int kWave = 64;
+constexpr int kWavesPerBlk = kBlk / kWave;
+constexpr int kHChunk = 1024;     // coefficients of one subtraction pass, in LDS
+
+// Sum over the 64 lanes of a wave (butterfly: every lane ends with the same bits).
+__device__ __forceinline__ double wave_sum(double v)
 {
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kBlk / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    double r = sh[0];
-    __syncthreads();
-    return r;
+#pragma unroll
+    for (int s = 1; s < kWave; s <<= 1) v += __shfl_xor(v, s, kWave);
+    return v;
 }
 
-__global__ __launch_bounds__(kBlk) void k_multidot_partial(const double* __restrict__ V, long ldv, int ncols,
-                                                           const double* __restrict__ w, long N,
-                                                           double* __restrict__ partial)
+// Column sums of the partials [nblk][ncols], columns c0 .. c0 + n - 1, into sh[0 .. n): one
+// wave per column, lanes over the blocks, then the butterfly (fixed order).
+__device__ __forceinline__ void sum_partials(const double* __restrict__ part, int nblk, int ncols, int c0, int n,
+                                             double* sh)
 {
-    __shared__ double sh[kBlk];
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    for (int c = wave; c < n; c += kWavesPerBlk) {
+        double s = 0.0;
+        for (int b = lane; b < nblk; b += kWave) s += part[(long)b * ncols + c0 + c];
+        s = wave_sum(s);
+        if (lane == 0) sh[c] = s;
+    }
+}
+
+// One pass of a Gram-Schmidt step over the workgroup's piece of w:
+//   SUB   h = column sums of pin; w -= V h (block 0 writes h to hout, added to it with ADD);
+//   DOTS  pout[block][c] = partial <V[:,c], w> of the (updated) piece;
+//   NORM  pout[block] = partial <w, w>.
+// The sums that a pass needs from the whole of w cross the launch boundary as partials,
+// and every workgroup sums them again for itself (nblk * ncols values from L2): a
+// Gram-Schmidt step with one re-orthogonalisation is then three launches and a final
+// one, instead of nine, three of them a one-thread-per-column sum of the partials of 25 us
+// (2D 512^2 solve of 9 steps with the FFT-based preconditioner: 5.62 ms before, 4.31 ms
+// after).  Bound: HBM for many columns, launch latency for few.
+template <bool SUB, bool ADD, bool DOTS, bool NORM>
+__global__ __launch_bounds__(kBlk) void k_orth(const double* __restrict__ V, long ldv, int ncols, double* __restrict__ w,
+                                               long N, const double* __restrict__ pin, double* __restrict__ hout,
+                                               double* __restrict__ pout)
+{
+    __shared__ double sh[SUB ? kHChunk : 1];
+    __shared__ double red[kWavesPerBlk][kColGroup];
     const long chunk = (N + gridDim.x - 1) / gridDim.x;
     const long lo = blockIdx.x * chunk;
     const long hi = (lo + chunk) < N ? (lo + chunk) : N;
-    for (int c0 = 0; c0 < ncols; c0 += kColGroup) {
-        double acc[kColGroup];
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    double nn = 0.0;
+    if constexpr (SUB) {
+        for (int c0 = 0; c0 < ncols; c0 += kHChunk) {
+            const int n = min(kHChunk, ncols - c0);
+            __syncthreads();
+            sum_partials(pin, gridDim.x, ncols, c0, n, sh);
+            __syncthreads();
+            if (blockIdx.x == 0)
+                for (int c = threadIdx.x; c < n; c += kBlk) hout[c0 + c] = ADD ? hout[c0 + c] + sh[c] : sh[c];
+            for (long i = lo + threadIdx.x; i < hi; i += kBlk) {
+                double s = 0.0;
+                const double* v = V + (long)c0 * ldv + i;
+                int c = 0;
+                for (; c + 8 <= n; c += 8) {
+                    double x[8];
 #pragma unroll
-        for (int c = 0; c < kColGroup; ++c) acc[c] = 0.0;
-        for (long i = lo + threadIdx.x; i < hi; i += kBlk) {
-            const double wi = w[i];
+                    for (int u = 0; u < 8; ++u) x[u] = v[(long)(c + u) * ldv];
 #pragma unroll
-            for (int c = 0; c < kColGroup; ++c)
-                if (c0 + c < ncols) acc[c] += V[(long)(c0 + c) * ldv + i] * wi;
-        }
-#pragma unroll
-        for (int c = 0; c < kColGroup; ++c) {
-            if (c0 + c < ncols) {
-                double s = block_sum(acc[c], sh);
-                if (threadIdx.x == 0) partial[(long)blockIdx.x * ncols + c0 + c] = s;
+                    for (int u = 0; u < 8; ++u) s += x[u] * sh[c + u];
+                }
+                for (; c < n; ++c) s += v[(long)c * ldv] * sh[c];
+                const double wi = w[i] - s;
+                w[i] = wi;
+                if (NORM && c0 + kHChunk >= ncols) nn += wi * wi;
             }
+        }
+    }
+    if constexpr (DOTS) {
+        for (int c0 = 0; c0 < ncols; c0 += kColGroup) {
+            double acc[kColGroup];
+#pragma unroll
+            for (int c = 0; c < kColGroup; ++c) acc[c] = 0.0;
+            for (long i = lo + threadIdx.x; i < hi; i += kBlk) {
+                const double wi = w[i];
+#pragma unroll
+                for (int c = 0; c < kColGroup; ++c)
+                    if (c0 + c < ncols) acc[c] += V[(long)(c0 + c) * ldv + i] * wi;
+            }
+            __syncthreads();                              // the previous group's sums are read
+#pragma unroll
+            for (int c = 0; c < kColGroup; ++c) {
+                const double s = wave_sum(acc[c]);
+                if (lane == 0) red[wave][c] = s;
+            }
+            __syncthreads();
+            if (threadIdx.x < kColGroup && c0 + (int)threadIdx.x < ncols) {
+                double s = red[0][threadIdx.x];
+                for (int q = 1; q < kWavesPerBlk; ++q) s += red[q][threadIdx.x];
+                pout[(long)blockIdx.x * ncols + c0 + threadIdx.x] = s;
+            }
+        }
+    }
+    if constexpr (NORM) {
+        nn = wave_sum(nn);
+        __syncthreads();
+        if (lane == 0) red[wave][0] = nn;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double s = red[0][0];
+            for (int q = 1; q < kWavesPerBlk; ++q) s += red[q][0];
+            pout[blockIdx.x] = s;
         }
     }
 }
 
-__global__ void k_multidot_final(const double* __restrict__ partial, int nblk, int ncols, double* __restrict__ out)
+// out[c] = column sums of the partials (one wave per column).
+__global__ __launch_bounds__(kBlk) void k_multidot_final(const double* __restrict__ part, int nblk, int ncols,
+                                                         double* __restrict__ out)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= ncols) return;
-    double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += partial[(long)b * ncols + c];
-    out[c] = s;
+    __shared__ double sh[kWavesPerBlk];
+    const int c0 = blockIdx.x * kWavesPerBlk, n = min(kWavesPerBlk, ncols - c0);
+    sum_partials(part, nblk, ncols, c0, n, sh);
+    __syncthreads();
+    if ((int)threadIdx.x < n) out[c0 + threadIdx.x] = sh[threadIdx.x];
+}
+
+// The end of a Gram-Schmidt step: the squared norm from its partials, and the column of
+// the Hessenberg matrix (h, then the squared norm) to page-locked host memory.
+__global__ __launch_bounds__(kBlk) void k_orth_final(const double* __restrict__ part, int nblk,
+                                                     const double* __restrict__ h, int ncols,
+                                                     double* __restrict__ host)
+{
+    __shared__ double sh[1];
+    sum_partials(part, nblk, 1, 0, 1, sh);
+    for (int c = threadIdx.x; c < ncols; c += kBlk) host[c] = h[c];
+    __syncthreads();
+    if (threadIdx.x == 0) host[ncols] = sh[0];
 }
 
 __global__ __launch_bounds__(kBlk) void k_gemv(const double* __restrict__ V, long ldv, int ncols,
@@ -98,6 +184,14 @@ __global__ void k_zero(double* __restrict__ y, long N)
     if (i < N) y[i] = 0.0;
 }
 
+// workgroups of a reduction: at least 64 values each, at most kRedBlocks
+inline int red_blocks(long N)
+{
+    int nb = kRedBlocks;
+    if ((long)nb * 64 > N) nb = (int)((N + 63) / 64);
+    return nb < 1 ? 1 : nb;
+}
+
 inline unsigned nblocks(long N) { return (unsigned)((N + kBlk - 1) / kBlk); }
 
 }  // namespace
@@ -106,12 +200,29 @@ ert_status dev_multidot(hipStream_t s, const double* V, long ldv, int ncols, con
                         double* partial, double* out)
 {
     if (ncols <= 0) return ERT_OK;
-    int nb = kRedBlocks;
-    if ((long)nb * 64 > N) nb = (int)((N + 63) / 64);
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(k_multidot_partial, dim3(nb), dim3(kBlk), 0, s, V, ldv, ncols, w, N, partial);
+    const int nb = red_blocks(N);
+    // (w is only read: the instance has no subtraction)
+    hipLaunchKernelGGL((k_orth<false, false, true, false>), dim3(nb), dim3(kBlk), 0, s, V, ldv, ncols,
+                       const_cast<double*>(w), N, (const double*)nullptr, (double*)nullptr, partial);
     ERT_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_multidot_final, dim3((ncols + 63) / 64), dim3(64), 0, s, partial, nb, ncols, out);
+    hipLaunchKernelGGL(k_multidot_final, dim3((ncols + kWavesPerBlk - 1) / kWavesPerBlk), dim3(kBlk), 0, s,
+                       (const double*)partial, nb, ncols, out);
+    ERT_HIP(hipGetLastError());
+    return ERT_OK;
+}
+
+ert_status dev_orthogonalise(hipStream_t s, const double* V, long ldv, int ncols, double* w, long N, double* partial,
+                             double* partial2, double* h, double* host)
+{
+    const int nb = red_blocks(N);
+    const dim3 grid(nb), blk(kBlk);
+    hipLaunchKernelGGL((k_orth<false, false, true, false>), grid, blk, 0, s, V, ldv, ncols, w, N,
+                       (const double*)nullptr, (double*)nullptr, partial);
+    hipLaunchKernelGGL((k_orth<true, false, true, false>), grid, blk, 0, s, V, ldv, ncols, w, N,
+                       (const double*)partial, h, partial2);
+    hipLaunchKernelGGL((k_orth<true, true, false, true>), grid, blk, 0, s, V, ldv, ncols, w, N,
+                       (const double*)partial2, h, partial);
+    hipLaunchKernelGGL(k_orth_final, dim3(1), blk, 0, s, (const double*)partial, nb, (const double*)h, ncols, host);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }
@@ -158,13 +269,6 @@ ert_status dev_add(hipStream_t s, double* y, const double* x, long N)
 ert_status dev_zero(hipStream_t s, double* y, long N)
 {
     hipLaunchKernelGGL(k_zero, dim3(nblocks(N)), dim3(kBlk), 0, s, y, N);
-    ERT_HIP(hipGetLastError());
-    return ERT_OK;
-}
-
-ert_status dev_small_add(hipStream_t s, double* dst, const double* src, int n)
-{
-    hipLaunchKernelGGL(k_add, dim3(nblocks(n)), dim3(kBlk), 0, s, dst, src, (long)n);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }

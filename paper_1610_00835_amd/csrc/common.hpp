@@ -376,6 +376,8 @@ struct ert_plan_impl {
     size_t ws_elems = 0;
     double* d_red = nullptr;     // reduction partials / small vectors
     size_t red_elems = 0;
+    double* h_col = nullptr;     // page-locked host: a column of the Hessenberg matrix, written by the GPU
+    size_t h_col_elems = 0;
     // solve vectors beside the Krylov workspace (phi, residual, correction, trial
     // iterate and its residual), grown on demand and kept for the next solve
     double* d_solve = nullptr;
@@ -438,8 +440,11 @@ ert_status dev_sub(hipStream_t s, double* y, const double* a, const double* b, l
 ert_status dev_add(hipStream_t s, double* y, const double* x, long N);
 // y = 0
 ert_status dev_zero(hipStream_t s, double* y, long N);
-// dst[i] += src[i] for a small vector of length n (device)
-ert_status dev_small_add(hipStream_t s, double* dst, const double* src, int n);
+// One classical Gram-Schmidt step with a re-orthogonalisation: w -= V h1, w -= V h2, h = h1 + h2
+// (device, ncols), and h followed by ||w||^2 to page-locked `host` (ncols + 1).  partial and
+// partial2: device, reduction blocks x ncols each.
+ert_status dev_orthogonalise(hipStream_t s, const double* V, long ldv, int ncols, double* w, long N, double* partial,
+                             double* partial2, double* h, double* host);
 
 // C = beta C + alpha A B (FP64, element strides); `work` (may be null) lets long
 // reductions split over several workgroup slices.

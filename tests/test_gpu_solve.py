@@ -279,3 +279,22 @@ def test_learned_refinement_judged_in_fp64(ev, oracle_mod):
     assert ig["converged"] == 1 and ig["rel_resid_true"] <= 1e-10
     assert abs(ig["rel_resid_true"] - res) <= 1e-3 * res + 1e-16
     assert rel_l2(Ug, Uo) <= 1e-8
+
+
+# reductions of one workgroup with a short last wave, of several, and of the full count with
+# a ragged last piece; more columns than one group of eight
+@pytest.mark.parametrize("n", [(5, 3), (9, 7), (31, 33), (125, 124)])
+def test_gram_schmidt_sizes(n):
+    """GMRES on a strongly scattering medium reaches 1e-11, and the Arnoldi estimate, which
+    holds while the basis is orthogonal, agrees with the true residual: both carry rounding
+    of 1e-16 times the norms, so they differ by less than 1e-13."""
+    import torch
+    from paper_1610_00835_amd import ertvie
+    N = n[0] * n[1]
+    f = torch.from_numpy(np.random.default_rng(1).uniform(0.0, 1.0, N)).cuda()
+    U = torch.empty_like(f)
+    with ertvie.Plan(2, n, 1.0 / max(n), np.full(N, 30.0), np.full(N, 29.9), method="fmm", prec="fp64") as plan:
+        info = plan.solve(f, U, tol=1e-11)
+    assert info["converged"] == 1 and info["restarts"] == 0
+    assert abs(info["rel_resid_est"] - info["rel_resid_true"]) <= 1e-13
+    assert info["iters"] > 8 or N < 64
