@@ -10,9 +10,23 @@
 // axis, coarse sigma_t / sigma_s the averages of the children, rediscretised
 // with 2h; red-black Gauss-Seidel (red = even i0+i1+i2 first), 2 sweeps before
 // and after the coarse correction; restriction by averaging the children,
-// constant prolongation; the coarsest level gets 60 sweeps in one workgroup.
-// All FP64 (the smoother's sums in a fixed order: per axis z, y, x, the upper
-// neighbour before the lower).
+// constant prolongation; 60 sweeps on the coarsest level.  All FP64.
+//
+// How a cycle runs.  The work is a few hundred dependent half-sweeps over small
+// arrays, so what bounds it is the number of dependent launches:
+//  - The cycle below a level of at most kDenseCells cells, started from zero, is a
+//    fixed linear map of the level's right-hand side.  Its matrix is formed once,
+//    one unit vector per workgroup (k_small_matrix), and every cycle then applies
+//    it as one matrix-vector product (k_dense) instead of about 170 dependent
+//    half-sweeps of one workgroup (177 us at 2D 264^2).
+//  - 2D levels above it take one launch down (both pre-sweeps, residual and
+//    restriction) and one up (prolongation and both post-sweeps) over LDS tiles with
+//    a halo as wide as the half-sweeps reach (k_tile), instead of five and five.
+//    With both, a 2D 264^2 solve of 10 steps takes 4.40 ms instead of 10.7.
+//  - In 3D such tiles would be mostly halo (an 8^3 tile of an 18^3 box), so the
+//    larger levels keep one launch per half-sweep.
+// Face coefficients are stored divided by h^2 and the smoother multiplies by the
+// inverse diagonal.
 #include "common.hpp"
 
 #include <algorithm>
@@ -26,16 +40,18 @@ struct DiffLevel {
     long N = 0;
     double* st = nullptr;
     double* ss = nullptr;
-    double* diag = nullptr;
-    double* df[3] = {nullptr, nullptr, nullptr};   // face to the upper neighbour along axis a
-    double* U = nullptr;
+    double* idiag = nullptr;                       // 1 / diagonal
+    double* df[3] = {nullptr, nullptr, nullptr};   // face to the upper neighbour along axis a, over h^2
+    double* U = nullptr;                           // iterate after the pre-sweeps
+    double* V = nullptr;                           // 2D: iterate after the post-sweeps (tiles read U's halos)
     double* B = nullptr;
 };
 
 struct DiffPc {
     int dim = 0;
     std::vector<DiffLevel> lv;
-    double* rhs = nullptr;
+    int dense = 0;               // level whose cycle is the matrix `mat`
+    double* mat = nullptr;       // [n][n], row major, n = cells of level `dense`
     long bytes = 0;
 };
 
@@ -43,12 +59,15 @@ namespace {
 
 constexpr int kPre = 2, kPost = 2, kCoarseSweeps = 60, kCoarsest = 4, kCycles = 2;
 
+constexpr int kDenseCells = 512;   // 2 MB of matrix; one thread per cell of a workgroup forms its columns
+constexpr int kMaxSmall = 8;       // levels of at most kDenseCells cells (a 512 x 1 grid has 8)
+
 struct LvArgs {
     int dim, n0, n1, n2;
     double h;
     const double* st;
     const double* ss;
-    double* diag;
+    double* idiag;
     double* dfx;
     double* dfy;
     double* dfz;
@@ -97,7 +116,7 @@ __global__ void k_faces(LvArgs a)
         double v = 0.0;
         if (ax < a.dim && i[ax] < n[ax] - 1) {
             const double Dk = 1.0 / (a.dim * a.st[j + s[ax]]);
-            v = 2.0 * Dj * Dk / (Dj + Dk);
+            v = 2.0 * Dj * Dk / (Dj + Dk) / (a.h * a.h);
         }
         df[ax][j] = v;
     }
@@ -113,155 +132,286 @@ __global__ void k_diag(LvArgs a)
     const int n[3] = {a.n0, a.n1, a.n2};
     const long s[3] = {1, a.n0, (long)a.n0 * a.n1};
     const double* df[3] = {a.dfx, a.dfy, a.dfz};
-    const double h2 = a.h * a.h;
     const double Dj = 1.0 / (a.dim * a.st[j]);
     const double rob = 2.0 * Dj / (a.h * (a.h + 4.0 * Dj));
     double d = a.st[j] - a.ss[j];
     for (int ax = a.dim - 1; ax >= 0; --ax) {
-        if (i[ax] < n[ax] - 1) d += df[ax][j] / h2;
-        if (i[ax] > 0) d += df[ax][j - s[ax]] / h2;
+        if (i[ax] < n[ax] - 1) d += df[ax][j];
+        if (i[ax] > 0) d += df[ax][j - s[ax]];
         if (i[ax] == 0) d += rob;
         if (i[ax] == n[ax] - 1) d += rob;
     }
-    a.diag[j] = d;
+    a.idiag[j] = 1.0 / d;
 }
 
-// sum over interior faces of Df U_k / h^2, per axis z, y, x: upper then lower neighbour
-__device__ __forceinline__ double offdiag(const LvArgs& a, const double* __restrict__ U, long j, const int i[3])
+// sum over interior faces of (Df / h^2) U_k (a face on the boundary has a zero coefficient)
+__device__ __forceinline__ double offdiag(const LvArgs& a, const double* U, int j, int x, int y, int z)
 {
-    const int n[3] = {a.n0, a.n1, a.n2};
-    const long s[3] = {1, a.n0, (long)a.n0 * a.n1};
-    const double* df[3] = {a.dfx, a.dfy, a.dfz};
-    const double h2 = a.h * a.h;
     double o = 0.0;
-    for (int ax = a.dim - 1; ax >= 0; --ax) {
-        if (i[ax] < n[ax] - 1) o += df[ax][j] * U[j + s[ax]] / h2;
-        if (i[ax] > 0) o += df[ax][j - s[ax]] * U[j - s[ax]] / h2;
+    if (a.dim > 2) {
+        const int s2 = a.n0 * a.n1;
+        if (z < a.n2 - 1) o += a.dfz[j] * U[j + s2];
+        if (z > 0) o += a.dfz[j - s2] * U[j - s2];
     }
+    if (y < a.n1 - 1) o += a.dfy[j] * U[j + a.n0];
+    if (y > 0) o += a.dfy[j - a.n0] * U[j - a.n0];
+    if (x < a.n0 - 1) o += a.dfx[j] * U[j + 1];
+    if (x > 0) o += a.dfx[j - 1] * U[j - 1];
     return o;
 }
 
+// One colour of a 3D level: thread = one cell of the colour (two per x pair).
 __global__ __launch_bounds__(256) void k_rbgs(LvArgs a, double* __restrict__ U, const double* __restrict__ B,
                                               int colour)
 {
-    const long N = (long)a.n0 * a.n1 * a.n2;
-    const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    int i[3];
-    unravel(j, a.n0, a.n1, i);
-    if (((i[0] + i[1] + i[2]) & 1) != colour) return;
-    U[j] = (B[j] + offdiag(a, U, j, i)) / a.diag[j];
+    const int hx = (a.n0 + 1) / 2;
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= hx * a.n1 * a.n2) return;
+    const int r = t / hx, y = r % a.n1, z = r / a.n1;
+    const int x = 2 * (t - r * hx) + ((y + z + colour) & 1);
+    if (x >= a.n0) return;
+    const int j = x + a.n0 * r;
+    U[j] = (B[j] + offdiag(a, U, j, x, y, z)) * a.idiag[j];
 }
 
-// B_c = average over the children of the fine residual B - (diag U - offdiag U), and
-// U_c = 0 (the coarser correction starts from zero): coarse cell q
-__device__ __forceinline__ void restrict_residual(const LvArgs& a, const double* __restrict__ U,
-                                                  const double* __restrict__ B, long q, int c0, int c1,
-                                                  double* __restrict__ Bc, double* __restrict__ Uc)
-{
-    int ic[3];
-    unravel(q, c0, c1, ic);
-    double s = 0.0;
-    int cnt = 0;
-    for (int oz = 0; oz < (a.dim > 2 ? 2 : 1); ++oz)
-        for (int oy = 0; oy < 2; ++oy)
-            for (int ox = 0; ox < 2; ++ox) {
-                const int i[3] = {2 * ic[0] + ox, 2 * ic[1] + oy, 2 * ic[2] + oz};
-                if (i[0] < a.n0 && i[1] < a.n1 && i[2] < a.n2) {
-                    const long j = i[0] + (long)a.n0 * (i[1] + (long)a.n1 * i[2]);
-                    s += B[j] - (a.diag[j] * U[j] - offdiag(a, U, j, i));
-                    ++cnt;
-                }
-            }
-    Bc[q] = s / cnt;
-    Uc[q] = 0.0;
-}
-
+// B_c = average over the children of the residual B - (diag U - offdiag U), and U_c = 0
+// (the coarser correction starts from zero).
 __global__ __launch_bounds__(256) void k_restrict_residual(LvArgs a, const double* __restrict__ U,
                                                            const double* __restrict__ B, int c0, int c1, int c2,
                                                            double* __restrict__ Bc, double* __restrict__ Uc)
 {
-    const long q = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (q < (long)c0 * c1 * c2) restrict_residual(a, U, B, q, c0, c1, Bc, Uc);
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= c0 * c1 * c2) return;
+    const int r = q / c0, qx = q - r * c0, qy = r % c1, qz = r / c1;
+    double s = 0.0;
+    int cnt = 0;
+    for (int o = 0; o < 8; ++o) {
+        const int x = 2 * qx + (o & 1), y = 2 * qy + ((o >> 1) & 1), z = 2 * qz + (o >> 2);
+        if (x >= a.n0 || y >= a.n1 || z >= a.n2) continue;
+        const int j = x + a.n0 * (y + a.n1 * z);
+        s += B[j] - (U[j] / a.idiag[j] - offdiag(a, U, j, x, y, z));
+        ++cnt;
+    }
+    Bc[q] = s / cnt;
+    Uc[q] = 0.0;
 }
 
 __global__ void k_prolong_add(int f0, int f1, int f2, double* __restrict__ Uf, int c0, int c1,
                               const double* __restrict__ Ec)
 {
-    const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (j >= (long)f0 * f1 * f2) return;
-    int i[3];
-    unravel(j, f0, f1, i);
-    Uf[j] += Ec[(i[0] / 2) + (long)c0 * ((i[1] / 2) + (long)c1 * (i[2] / 2))];
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= f0 * f1 * f2) return;
+    const int r = j / f0, x = j - r * f0, y = r % f1, z = r / f1;
+    Uf[j] += Ec[x / 2 + c0 * (y / 2 + c1 * (z / 2))];
 }
 
-// The V-cycle below a level of at most kSmallCells cells, in one workgroup: the
-// same steps as the per-level launches (smoothing, residual, restriction, the
-// coarser cycle, prolongation, smoothing), each a workgroup-stride loop closed by
-// a barrier.  Red-black colours, residuals, averages and prolongations are per
-// cell, so the results equal the per-level launches bit for bit.
-constexpr int kSmallCells = 256;
-constexpr int kMaxSmall = 12;
+// ------------------------------------------------------------- 2D tiles ----
 
-struct SmallLevel {
-    LvArgs a;
-    long N;
-    double* U;
-    double* B;
+// One half of a cycle on a 2D level.  A workgroup owns a kTile x kTile tile and holds
+// the tile and a halo of kHalo cells in LDS (iterate) and registers (right-hand side
+// and coefficients of its cells).  The four half-sweeps run on the whole box; a
+// half-sweep spoils one more ring of cells, counted from the box's edge, and the
+// residual reads one ring further, so the tile's own values are exact.
+//   down (UP = false): U_out = smooth(U_in) (U_in = 0 when null), and the restricted
+//     residual to Bc.  The black cells' residual is zero after the last half-sweep.
+//     With r, the right-hand side is ss r, formed here and stored to Bout.
+//   up (UP = true): U_out = smooth(U_in + prolong(Ec)); with r, U_out receives
+//     r + that (the preconditioner's output; r and U_out may be the same buffer).
+// Neighbouring tiles read each other's U_in, so U_out is another buffer.
+// Bound: launch latency and the four barriers (2D 264^2: 81 workgroups, 7 cells per
+// thread); 32 x 32 tiles keep the halo's share at 1.7.
+constexpr int kTile = 32, kHalo = 5, kBox = kTile + 2 * kHalo, kPitch = kBox + 1;
+constexpr int kBoxPer = (kBox * kBox + 255) / 256;
+
+template <bool UP>
+__global__ __launch_bounds__(256) void k_tile(LvArgs a, const double* Uin, const double* Bin, const double* r,
+                                              const double* __restrict__ ss, int c0, int c1,
+                                              const double* __restrict__ Ec, double* Uout, double* Bout,
+                                              double* __restrict__ Bc)
+{
+    __shared__ double u[kBox * kPitch];
+    __shared__ double res[UP ? 1 : kTile * (kTile + 1)];
+    const int tx0 = blockIdx.x * kTile, ty0 = blockIdx.y * kTile;
+    double b[kBoxPer], id[kBoxPer], ce[kBoxPer], cw[kBoxPer], cn[kBoxPer], cs[kBoxPer];
+    int at[kBoxPer];                              // LDS index
+    unsigned red = 0, upd = 0;                    // bit k: cell k is red, is updated by the sweeps
+#pragma unroll
+    for (int k = 0; k < kBoxPer; ++k) {
+        const int e = threadIdx.x + 256 * k;
+        const int ex = e % kBox, ey = e / kBox, x = tx0 + ex - kHalo, y = ty0 + ey - kHalo;
+        const bool box = e < kBox * kBox;
+        const bool in = box && x >= 0 && x < a.n0 && y >= 0 && y < a.n1;
+        const int j = in ? x + a.n0 * y : 0;
+        at[k] = ex + kPitch * ey;
+        double v = 0.0;
+        b[k] = id[k] = ce[k] = cw[k] = cn[k] = cs[k] = 0.0;
+        if (in) {
+            if (UP) v = Uin[j] + Ec[(x >> 1) + c0 * (y >> 1)];
+            else if (Uin) v = Uin[j];
+            b[k] = (!UP && r) ? ss[j] * r[j] : Bin[j];
+            id[k] = a.idiag[j];
+            ce[k] = a.dfx[j];
+            cn[k] = a.dfy[j];
+            if (x > 0) cw[k] = a.dfx[j - 1];
+            if (y > 0) cs[k] = a.dfy[j - a.n0];
+        }
+        if (box) u[at[k]] = v;
+        if (in && ex > 0 && ex < kBox - 1 && ey > 0 && ey < kBox - 1) upd |= 1u << k;
+        if (((x + y) & 1) == 0) red |= 1u << k;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2 * (UP ? kPost : kPre); ++h) {
+        const unsigned todo = upd & ((h & 1) ? ~red : red);
+#pragma unroll
+        for (int k = 0; k < kBoxPer; ++k)
+            if (todo >> k & 1u) {
+                const int i = at[k];
+                const double o = cn[k] * u[i + kPitch] + cs[k] * u[i - kPitch] + ce[k] * u[i + 1] + cw[k] * u[i - 1];
+                u[i] = (b[k] + o) * id[k];
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kBoxPer; ++k) {
+        const int e = threadIdx.x + 256 * k;
+        const int ex = e % kBox - kHalo, ey = e / kBox - kHalo, x = tx0 + ex, y = ty0 + ey;
+        if (e >= kBox * kBox || ex < 0 || ex >= kTile || ey < 0 || ey >= kTile) continue;
+        double rv = 0.0;
+        if (x < a.n0 && y < a.n1) {
+            const int j = x + a.n0 * y, i = at[k];
+            if (UP) {
+                Uout[j] = r ? r[j] + u[i] : u[i];
+            } else {
+                Uout[j] = u[i];
+                if (r) Bout[j] = b[k];
+                if (red >> k & 1u) {
+                    const double o =
+                        cn[k] * u[i + kPitch] + cs[k] * u[i - kPitch] + ce[k] * u[i + 1] + cw[k] * u[i - 1];
+                    rv = b[k] - (u[i] / id[k] - o);
+                }
+            }
+        }
+        if (!UP) res[ex + (kTile + 1) * ey] = rv;
+    }
+    if (UP) return;
+    __syncthreads();
+    const int qx = threadIdx.x % (kTile / 2), qy = threadIdx.x / (kTile / 2);
+    const int X = tx0 / 2 + qx, Y = ty0 / 2 + qy;
+    if (qy >= kTile / 2 || X >= c0 || Y >= c1) return;
+    const double* p = res + 2 * qx + (kTile + 1) * 2 * qy;
+    const int cnt = (2 * X + 1 < a.n0 ? 2 : 1) * (2 * Y + 1 < a.n1 ? 2 : 1);
+    Bc[X + c0 * Y] = (p[0] + p[1] + p[kTile + 1] + p[kTile + 2]) / cnt;
+}
+
+// ---------------------------------------------------------- dense levels ----
+
+struct SmallLevels {
+    int nl;                       // levels from the dense one down to the coarsest
+    int cycles;                   // 1; 2 when the dense level is the finest (both cycles in the matrix)
+    LvArgs a[kMaxSmall];
 };
 
-struct SmallCycle {
-    int nl;                       // levels k0 .. k0 + nl - 1, the last the coarsest
-    SmallLevel lv[kMaxSmall];
-};
-
-__device__ __forceinline__ void small_rbgs(const SmallLevel& L, int sweeps)
+__device__ __forceinline__ void small_rbgs(const LvArgs& a, int N, double* U, const double* B, int sweeps)
 {
     for (int sw = 0; sw < sweeps; ++sw)
         for (int colour = 0; colour < 2; ++colour) {
-            for (long j = threadIdx.x; j < L.N; j += blockDim.x) {
-                int i[3];
-                unravel(j, L.a.n0, L.a.n1, i);
-                if (((i[0] + i[1] + i[2]) & 1) == colour) L.U[j] = (L.B[j] + offdiag(L.a, L.U, j, i)) / L.a.diag[j];
+            for (int j = threadIdx.x; j < N; j += blockDim.x) {
+                const int r = j / a.n0, x = j - r * a.n0, y = r % a.n1, z = r / a.n1;
+                if (((x + y + z) & 1) == colour) U[j] = (B[j] + offdiag(a, U, j, x, y, z)) * a.idiag[j];
             }
             __syncthreads();
         }
 }
 
-__global__ __launch_bounds__(256) void k_small_cycle(SmallCycle c)
+// Column blockIdx.x of the cycle's matrix: the cycle(s) from zero for that unit vector.
+__global__ __launch_bounds__(kDenseCells) void k_small_matrix(SmallLevels c, double* __restrict__ mat)
 {
-    // down: smooth, residual, restrict (the first level's U is the caller's)
-    for (int k = 0; k + 1 < c.nl; ++k) {
-        const SmallLevel& L = c.lv[k];
-        const SmallLevel& C = c.lv[k + 1];
-        small_rbgs(L, kPre);
-        for (long q = threadIdx.x; q < C.N; q += blockDim.x) restrict_residual(L.a, L.U, L.B, q, C.a.n0, C.a.n1, C.B, C.U);
-        __syncthreads();
+    __shared__ double Us[2 * kDenseCells], Bs[2 * kDenseCells];   // sum of the levels' cells < 2 kDenseCells
+    int off[kMaxSmall], cells[kMaxSmall], total = 0;
+    for (int k = 0; k < c.nl; ++k) {
+        off[k] = total;
+        cells[k] = c.a[k].n0 * c.a[k].n1 * c.a[k].n2;
+        total += cells[k];
     }
-    // coarsest: sweeps on the correction equation from zero (zeroed above); a single-level
-    // hierarchy's only level is the finest, whose cycles continue from the current iterate
-    small_rbgs(c.lv[c.nl - 1], kCoarseSweeps);
-    // up: prolongate and smooth
-    for (int k = c.nl - 2; k >= 0; --k) {
-        const SmallLevel& L = c.lv[k];
-        const SmallLevel& C = c.lv[k + 1];
-        for (long j = threadIdx.x; j < L.N; j += blockDim.x) {
-            int i[3];
-            unravel(j, L.a.n0, L.a.n1, i);
-            L.U[j] += C.U[(i[0] / 2) + (long)C.a.n0 * ((i[1] / 2) + (long)C.a.n1 * (i[2] / 2))];
+    for (int j = threadIdx.x; j < total; j += blockDim.x) {
+        Us[j] = 0.0;
+        Bs[j] = j == (int)blockIdx.x ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    for (int cy = 0; cy < c.cycles; ++cy) {
+        for (int k = 0; k + 1 < c.nl; ++k) {
+            const LvArgs& a = c.a[k];
+            const LvArgs& q = c.a[k + 1];
+            double *U = Us + off[k], *B = Bs + off[k];
+            small_rbgs(a, cells[k], U, B, kPre);
+            for (int t = threadIdx.x; t < cells[k + 1]; t += blockDim.x) {
+                const int r = t / q.n0, qx = t - r * q.n0, qy = r % q.n1, qz = r / q.n1;
+                double s = 0.0;
+                int cnt = 0;
+                for (int o = 0; o < 8; ++o) {
+                    const int x = 2 * qx + (o & 1), y = 2 * qy + ((o >> 1) & 1), z = 2 * qz + (o >> 2);
+                    if (x >= a.n0 || y >= a.n1 || z >= a.n2) continue;
+                    const int j = x + a.n0 * (y + a.n1 * z);
+                    s += B[j] - (U[j] / a.idiag[j] - offdiag(a, U, j, x, y, z));
+                    ++cnt;
+                }
+                Bs[off[k + 1] + t] = s / cnt;
+                Us[off[k + 1] + t] = 0.0;
+            }
+            __syncthreads();
         }
-        __syncthreads();
-        small_rbgs(L, kPost);
+        small_rbgs(c.a[c.nl - 1], cells[c.nl - 1], Us + off[c.nl - 1], Bs + off[c.nl - 1], kCoarseSweeps);
+        for (int k = c.nl - 2; k >= 0; --k) {
+            const LvArgs& a = c.a[k];
+            const LvArgs& q = c.a[k + 1];
+            double* U = Us + off[k];
+            for (int j = threadIdx.x; j < cells[k]; j += blockDim.x) {
+                const int r = j / a.n0, x = j - r * a.n0, y = r % a.n1, z = r / a.n1;
+                U[j] += Us[off[k + 1] + x / 2 + q.n0 * (y / 2 + q.n1 * (z / 2))];
+            }
+            __syncthreads();
+            small_rbgs(a, cells[k], U, Bs + off[k], kPost);
+        }
+    }
+    for (int j = threadIdx.x; j < cells[0]; j += blockDim.x) mat[(long)j * cells[0] + blockIdx.x] = Us[j];
+}
+
+// y = mat b, one wave per row.  FINEST: y = r + mat (ss r), the whole preconditioner of a
+// grid of at most kDenseCells cells; r and y may be the same buffer, so one workgroup
+// reads all of r before it writes.
+template <bool FINEST>
+__global__ __launch_bounds__(FINEST ? 1024 : 256) void k_dense(const double* __restrict__ mat, int n, const double* b,
+                                                              const double* __restrict__ ss, double* y)
+{
+    __shared__ double sb[kDenseCells];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) sb[i] = FINEST ? ss[i] * b[i] : b[i];
+    __syncthreads();
+    for (int row = blockIdx.x * nw + wave; row < n; row += gridDim.x * nw) {
+        const double* m = mat + (long)row * n;
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < kDenseCells / 64; ++k) {
+            const int i = 64 * k + lane;
+            if (i < n) s += m[i] * sb[i];
+        }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) s += __shfl_xor(s, d, 64);
+        if (lane == 0) y[row] = FINEST ? b[row] + s : s;
     }
 }
 
-__global__ void k_scaled(const double* __restrict__ r, const double* __restrict__ ss, long N, double* __restrict__ b)
+__global__ void k_scaled(const double* __restrict__ r, const double* __restrict__ ss, long N, double* __restrict__ b,
+                         double* __restrict__ u)
 {
     const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (j < N) b[j] = ss[j] * r[j];
+    if (j >= N) return;
+    b[j] = ss[j] * r[j];
+    u[j] = 0.0;
 }
 
-__global__ void k_add_out(const double* __restrict__ r, const double* __restrict__ u, long N, double* __restrict__ z)
+__global__ void k_add_out(const double* r, const double* __restrict__ u, long N, double* z)
 {
     const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (j < N) z[j] = r[j] + u[j];
@@ -271,50 +421,56 @@ inline unsigned nblk(long n) { return (unsigned)((n + 255) / 256); }
 
 LvArgs args_of(const DiffPc* d, const DiffLevel& L)
 {
-    return LvArgs{d->dim, L.n[0], L.n[1], L.n[2], L.h, L.st, L.ss, L.diag, L.df[0], L.df[1], L.df[2]};
+    return LvArgs{d->dim, L.n[0], L.n[1], L.n[2], L.h, L.st, L.ss, L.idiag, L.df[0], L.df[1], L.df[2]};
 }
 
-__global__ void k_zero(double* __restrict__ p, long n)
+ert_status dense(hipStream_t s, DiffPc* d)
 {
-    const long j = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (j < n) p[j] = 0.0;
-}
-
-ert_status zero(hipStream_t s, double* p, long n)
-{
-    hipLaunchKernelGGL(k_zero, dim3(nblk(n)), dim3(256), 0, s, p, n);
+    DiffLevel& L = d->lv[d->dense];
+    hipLaunchKernelGGL(k_dense<false>, dim3((unsigned)((L.N + 3) / 4)), dim3(256), 0, s, (const double*)d->mat, (int)L.N,
+                       (const double*)L.B, (const double*)nullptr, d->dim == 2 ? L.V : L.U);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }
 
-ert_status vcycle(hipStream_t s, DiffPc* d, int k)
+// One cycle from level k down in 2D.  first: the iterate starts at zero; r (finest level
+// only): the residual the preconditioner acts on; out: r + U instead of the level's V.
+ert_status vcycle2(hipStream_t s, DiffPc* d, int k, bool first, const double* r, double* out)
 {
+    if (k == d->dense) return dense(s, d);
     DiffLevel& L = d->lv[k];
-    const LvArgs a = args_of(d, L);
-    const int nl = (int)d->lv.size() - k;
-    if (k + 1 == (int)d->lv.size() || (L.N <= kSmallCells && nl <= kMaxSmall)) {
-        // this level and the coarser ones in one workgroup (the coarsest level always goes here)
-        SmallCycle c{};
-        c.nl = nl;
-        for (int q = 0; q < nl; ++q) {
-            DiffLevel& Q = d->lv[k + q];
-            c.lv[q] = SmallLevel{args_of(d, Q), Q.N, Q.U, Q.B};
-        }
-        hipLaunchKernelGGL(k_small_cycle, dim3(1), dim3(256), 0, s, c);
-        ERT_HIP(hipGetLastError());
-        return ERT_OK;
-    }
-    for (int sw = 0; sw < kPre; ++sw)
-        for (int c = 0; c < 2; ++c) hipLaunchKernelGGL(k_rbgs, dim3(nblk(L.N)), dim3(256), 0, s, a, L.U, L.B, c);
     DiffLevel& C = d->lv[k + 1];
+    const LvArgs a = args_of(d, L);
+    const dim3 grid((unsigned)((L.n[0] + kTile - 1) / kTile), (unsigned)((L.n[1] + kTile - 1) / kTile));
+    hipLaunchKernelGGL(k_tile<false>, grid, dim3(256), 0, s, a, first ? (const double*)nullptr : (const double*)L.V,
+                       (const double*)L.B, first ? r : nullptr, (const double*)L.ss, C.n[0], C.n[1],
+                       (const double*)nullptr, L.U, L.B, C.B);
+    ERT_HIP(hipGetLastError());
+    ERT_TRY(vcycle2(s, d, k + 1, true, nullptr, nullptr));
+    hipLaunchKernelGGL(k_tile<true>, grid, dim3(256), 0, s, a, (const double*)L.U, (const double*)L.B, out ? r : nullptr,
+                       (const double*)nullptr, C.n[0], C.n[1], (const double*)C.V, out ? out : L.V, (double*)nullptr,
+                       (double*)nullptr);
+    ERT_HIP(hipGetLastError());
+    return ERT_OK;
+}
+
+ert_status vcycle3(hipStream_t s, DiffPc* d, int k)
+{
+    if (k == d->dense) return dense(s, d);
+    DiffLevel& L = d->lv[k];
+    DiffLevel& C = d->lv[k + 1];
+    const LvArgs a = args_of(d, L);
+    const dim3 half(nblk((long)((L.n[0] + 1) / 2) * L.n[1] * L.n[2]));
+    for (int h = 0; h < 2 * kPre; ++h)
+        hipLaunchKernelGGL(k_rbgs, half, dim3(256), 0, s, a, L.U, (const double*)L.B, h & 1);
     hipLaunchKernelGGL(k_restrict_residual, dim3(nblk(C.N)), dim3(256), 0, s, a, (const double*)L.U,
                        (const double*)L.B, C.n[0], C.n[1], C.n[2], C.B, C.U);
     ERT_HIP(hipGetLastError());
-    ERT_TRY(vcycle(s, d, k + 1));
+    ERT_TRY(vcycle3(s, d, k + 1));
     hipLaunchKernelGGL(k_prolong_add, dim3(nblk(L.N)), dim3(256), 0, s, L.n[0], L.n[1], L.n[2], L.U, C.n[0], C.n[1],
                        (const double*)C.U);
-    for (int sw = 0; sw < kPost; ++sw)
-        for (int c = 0; c < 2; ++c) hipLaunchKernelGGL(k_rbgs, dim3(nblk(L.N)), dim3(256), 0, s, a, L.U, L.B, c);
+    for (int h = 0; h < 2 * kPost; ++h)
+        hipLaunchKernelGGL(k_rbgs, half, dim3(256), 0, s, a, L.U, (const double*)L.B, h & 1);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }
@@ -343,9 +499,10 @@ ert_status diffpc_build(ert_plan_impl* p)
         L.N = (long)n[0] * n[1] * n[2];
         alloc(&L.st, L.N);
         alloc(&L.ss, L.N);
-        alloc(&L.diag, L.N);
+        alloc(&L.idiag, L.N);
         for (int a = 0; a < 3; ++a) alloc(&L.df[a], L.N);
         alloc(&L.U, L.N);
+        if (d->dim == 2) alloc(&L.V, L.N);
         alloc(&L.B, L.N);
         d->lv.push_back(L);
         if (st != ERT_OK) break;
@@ -354,7 +511,12 @@ ert_status diffpc_build(ert_plan_impl* p)
         for (int a = 0; a < 3; ++a) n[a] = (n[a] + 1) / 2;
         h *= 2.0;
     }
-    if (st == ERT_OK) alloc(&d->rhs, p->N);
+    long nd = 0;
+    if (st == ERT_OK) {
+        while (d->lv[d->dense].N > kDenseCells) ++d->dense;   // the coarsest has at most 4^3
+        nd = d->lv[d->dense].N;
+        alloc(&d->mat, nd * nd);
+    }
     if (st == ERT_OK) {
         DiffLevel& L0 = d->lv[0];
         st = ERT_HIPST(hipMemcpyAsync(L0.st, p->d_st, sizeof(double) * L0.N, hipMemcpyDeviceToDevice, s));
@@ -375,6 +537,14 @@ ert_status diffpc_build(ert_plan_impl* p)
             hipLaunchKernelGGL(k_diag, dim3(nblk(d->lv[k].N)), dim3(256), 0, s, a);
             st = ERT_HIPST(hipGetLastError());
         }
+        if (st == ERT_OK) {
+            SmallLevels c{};
+            c.nl = (int)d->lv.size() - d->dense;
+            c.cycles = d->dense == 0 ? kCycles : 1;
+            for (int q = 0; q < c.nl; ++q) c.a[q] = args_of(d, d->lv[d->dense + q]);
+            hipLaunchKernelGGL(k_small_matrix, dim3((unsigned)nd), dim3(kDenseCells), 0, s, c, d->mat);
+            st = ERT_HIPST(hipGetLastError());
+        }
         if (st == ERT_OK) st = ERT_HIPST(hipStreamSynchronize(s));
     }
     if (st != ERT_OK) {
@@ -393,12 +563,13 @@ void diffpc_destroy(DiffPc* d)
     for (auto& L : d->lv) {
         (void)hipFree(L.st);
         (void)hipFree(L.ss);
-        (void)hipFree(L.diag);
+        (void)hipFree(L.idiag);
         for (auto* q : L.df) (void)hipFree(q);
         (void)hipFree(L.U);
+        (void)hipFree(L.V);
         (void)hipFree(L.B);
     }
-    (void)hipFree(d->rhs);
+    (void)hipFree(d->mat);
     delete d;
 }
 
@@ -411,12 +582,19 @@ ert_status diffpc_apply(ert_plan_impl* p, const double* r, double* z, int nrhs)
     for (int c = 0; c < nrhs; ++c) {
         const double* rc = r + (size_t)c * p->N;
         double* zc = z + (size_t)c * p->N;
-        hipLaunchKernelGGL(k_scaled, dim3(nblk(p->N)), dim3(256), 0, s, rc, (const double*)p->d_ss, p->N, L0.B);
-        ERT_HIP(hipGetLastError());
-        ERT_TRY(zero(s, L0.U, L0.N));
-        for (int cy = 0; cy < kCycles; ++cy) ERT_TRY(vcycle(s, d, 0));
-        hipLaunchKernelGGL(k_add_out, dim3(nblk(p->N)), dim3(256), 0, s, rc, (const double*)L0.U, p->N, zc);
-        ERT_HIP(hipGetLastError());
+        if (d->dense == 0) {
+            hipLaunchKernelGGL(k_dense<true>, dim3(1), dim3(1024), 0, s, (const double*)d->mat, (int)p->N, rc,
+                               (const double*)p->d_ss, zc);
+            ERT_HIP(hipGetLastError());
+        } else if (d->dim == 2) {
+            for (int cy = 0; cy < kCycles; ++cy)
+                ERT_TRY(vcycle2(s, d, 0, cy == 0, rc, cy + 1 == kCycles ? zc : nullptr));
+        } else {
+            hipLaunchKernelGGL(k_scaled, dim3(nblk(p->N)), dim3(256), 0, s, rc, (const double*)p->d_ss, p->N, L0.B, L0.U);
+            for (int cy = 0; cy < kCycles; ++cy) ERT_TRY(vcycle3(s, d, 0));
+            hipLaunchKernelGGL(k_add_out, dim3(nblk(p->N)), dim3(256), 0, s, rc, (const double*)L0.U, p->N, zc);
+            ERT_HIP(hipGetLastError());
+        }
     }
     return ERT_OK;
 }

@@ -40,6 +40,25 @@ def test_diff_precond_matches_reference(ev, name, n):
     assert np.array_equal(z1, Z[:, 1])
 
 
+# the edges of the forms: one dense level (512 cells, 2D and 3D, and one past it), tiles of
+# 32 with one, exact and ragged remainders, one-cell axes, several tiled levels
+@pytest.mark.parametrize("name,n", [("c1", (32, 16)), ("c1", (27, 19)), ("c5", (8, 8, 8)), ("c5", (9, 8, 8)),
+                                    ("c1", (512, 1)), ("c1", (700, 1)), ("c1", (1, 33)), ("c3", (33, 47)),
+                                    ("c3", (64, 32)), ("c3", (65, 97)), ("c3", (130, 250)), ("c5", (70, 1, 9))])
+def test_diff_precond_forms(ev, name, n):
+    case = inputs.make_case(name, n=n, seed=3)
+    N = int(np.prod(n))
+    R = np.random.default_rng(4).standard_normal((N, 2))
+    with ev.plan_from_case(case, method="direct", prec="fp64", nrhs_max=2) as plan:
+        Z = to_host(plan.diff_precond(to_dev(R), to_dev(np.zeros((N, 2)))))
+        r1 = to_dev(R[:, 1])
+        z1 = to_host(plan.diff_precond(r1, r1))
+    for k in range(2):
+        ref = Dm.apply(R[:, k], case["dim"], case["n"], case["h"], case["sigma_t"], case["sigma_s"])
+        assert rel_l2(Z[:, k], ref) <= 1e-12
+    assert np.array_equal(z1, Z[:, 1])
+
+
 def test_diff_precond_full_size(ev):
     case = inputs.make_case("c5", n=(128, 128, 128), seed=0)
     N = 128 ** 3
