@@ -1456,6 +1456,14 @@ struct FmmImpl : FmmData {
     T* stage = nullptr;                 // staging rows of the far-field products
     T* stage_near = nullptr;            // staging rows of the near-field products (runs concurrently)
     size_t stage_near_elems = 0;
+    size_t rows_near = 0, rows_far = 0; // heterogeneous: staging rows of a pass that the buffers hold
+    size_t near_row() const { return (size_t)tr.nleaf * (tr.D == 3 ? 27 : 9) * tr.S; }
+    size_t far_row() const
+    {
+        size_t n = 0;
+        for (int l = 2; l <= tr.L; ++l) n = std::max(n, (size_t)hc->hnd[l] * tr.Kp);
+        return n;
+    }
     // the near field and the far-field passes are independent until L2P: after the
     // first (tuning) apply of a rhs bucket the near field runs on a second stream,
     // forked from and joined back to the apply's stream (also inside captured graphs)
@@ -2237,13 +2245,11 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
     };
     ERT_TRY(site_need(near_site, tr.nleaf, tr.S, sn_need));
     if (hetero) {
-        // staging rows (one per directed pair) per pass: kPairStreamRhs right-hand sides
-        // streamed, 64 on the matrix cores (from kPairMfmaMinRhs on, and always for the
-        // split-BF16x3 translations)
-        const size_t rb = (size_t)std::min(nrhs, nrhs >= kPairMfmaMinRhs ? 64 : kPairStreamRhs);
-        const size_t rbf = (size_t)std::min(nrhs, (nrhs >= kPairMfmaMinRhs || prec == ERT_BF16X3) ? 64 : kPairStreamRhs);
-        sn_need = std::max(sn_need, rb * tr.nleaf * (tr.D == 3 ? 27 : 9) * tr.S);
-        for (int l = 2; l <= tr.L; ++l) st_need = std::max(st_need, rbf * hc->hnd[l] * tr.Kp);
+        // staging rows (one per directed pair) of a pass of the products
+        rows_near = pair_rows(prec == ERT_FP64 ? ERT_FP64 : ERT_FP32, tr.S, nrhs);
+        rows_far = pair_rows(prec, tr.Kp, nrhs);
+        sn_need = std::max(sn_need, rows_near * near_row());
+        st_need = std::max(st_need, rows_far * far_row());
     }
     for (int l = 2; l <= tr.L; ++l)
         ERT_TRY(site_need(far_site[l], tr.nbox[l], rp[l] > 0 ? rp[l] : tr.Kp, st_need));
@@ -2256,8 +2262,14 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
         *have = need;
         return ERT_OK;
     };
-    ERT_TRY(grow(&stage, &stage_elems, st_need));
-    ERT_TRY(grow(&stage_near, &stage_near_elems, sn_need));
+    if (grow(&stage, &stage_elems, st_need) != ERT_OK || grow(&stage_near, &stage_near_elems, sn_need) != ERT_OK) {
+        // FP64 passes work with as few rows as the streaming ones have
+        if (!hetero || prec != ERT_FP64 || nrhs <= kPairStreamRhs) return ERT_EDEVICE;
+        (void)hipGetLastError();
+        rows_near = rows_far = kPairStreamRhs;
+        ERT_TRY(grow(&stage, &stage_elems, rows_far * far_row()));
+        ERT_TRY(grow(&stage_near, &stage_near_elems, rows_near * near_row()));
+    }
     if (tu_need > tune_elems) {
         if (tune) (void)hipFree(tune);
         tune = nullptr;
@@ -2448,6 +2460,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
             a.nsrc = tr.nleaf;
             a.W = q;
             a.stage = stage_near;
+            a.rows = rows_near;
             a.L = pot;
             a.accumulate = 0;
             st_.pause();
@@ -2533,6 +2546,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
                 a.nsrc = tr.nbox[l];
                 a.W = W[l];
                 a.stage = stage;
+                a.rows = rows_far;
                 a.L = Lc[l];
                 a.accumulate = first ? 0 : 1;
                 st_.pause();

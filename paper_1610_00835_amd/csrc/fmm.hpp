@@ -173,7 +173,8 @@ struct PairStream {
     int M;
     long nsrc;               // boxes (W is [B][nsrc][M])
     const void* W;
-    void* stage;             // [rows per pass][nrows][M]: 4 per streaming pass, 64 on the matrix cores
+    void* stage;             // [rows][nrows][M]
+    size_t rows;             // right-hand sides it holds: pair_rows(), or (FP64) at least kPairStreamRhs
     void* L;                 // [B][ntarget][M]
     int accumulate;
     // stage timing (ert_vie_profile): the pair products under prof_stage, their
@@ -182,11 +183,32 @@ struct PairStream {
     int prof_stage = 0;
 };
 
-// From this many right-hand sides on, cached-pair products run on the matrix cores
-// (64 right-hand sides per pass over the blocks; stage then holds min(B, 64) rows).
+// From this many right-hand sides on, FP32 cached-pair products run on the matrix cores
+// (64 right-hand sides per pass over the blocks).
 constexpr int kPairMfmaMinRhs = 16;
-// Staging rows per pass of the streaming form.
-constexpr int kPairStreamRhs = 4;
+// From this many on, FP64 ones do (16, 32 or 64 per pass; pairs.hip): a pass of 16 takes
+// 1.47 ms where streaming takes 0.87 ms per 2 and 1.5 ms per 4 (45 x 38 x 51, order 6).
+constexpr int kPairDualMinRhs = 3;
+// Right-hand sides of a pass: streaming form, FP64 and FP32 matrix-core forms.
+constexpr int kPairStreamRhs = 4, kPairDualRhs = 32, kPairMfmaRhs = 64;
+
+// FP64, `left` right-hand sides still to do: whether the next pass takes 64 in two
+// launches, 7 % faster than two passes of 32 (48^3, order 6: 6.5 against 6.9 ms) where 64
+// columns are nearly full and the blocks give its 256-row tiles enough to do; 2D blocks
+// of 64 rows take 0.64 ms instead of 1.24 in passes of 32.
+inline bool pair_pass64(int M, int left) { return left > 48 && M > 128; }
+
+// Staging rows (right-hand sides of one pass) of the products of M x M blocks for nrhs
+// right-hand sides.
+inline int pair_rows(int prec, int M, int nrhs)
+{
+    const bool pieces = M % 4 == 0;      // matrix-core forms take whole 4-value pieces
+    int rows = kPairStreamRhs;
+    if (prec == ERT_BF16X3) rows = kPairMfmaRhs;
+    else if (prec == ERT_FP64 && pieces && nrhs >= kPairDualMinRhs) rows = pair_pass64(M, nrhs) ? kPairMfmaRhs : kPairDualRhs;
+    else if (prec == ERT_FP32 && pieces && nrhs >= kPairMfmaMinRhs) rows = kPairMfmaRhs;
+    return nrhs < rows ? nrhs : rows;
+}
 
 // Blocks made on demand (FP32 storage): the products take the pairs in chunks of
 // `chunk`, each written into `scratch` by `fill` (kernel launches on the stream only)

@@ -14,13 +14,15 @@
 // goes to the staging row of its directed pair; a second pass sums the rows of
 // every target in a fixed order, so results are bitwise reproducible.
 //
-// Forms.  Up to 8 right-hand sides (passes of at most 4): one workgroup per
+// Forms.  Few right-hand sides (passes of at most 4): one workgroup per
 // block streams it once from HBM into registers and forms both products
 // (HBM-bound: each stored value is read once per pass).  From
-// kPairMfmaMinRhs right-hand sides on, and for the split-BF16x3 products always,
-// the matrix cores take 64 right-hand sides per pass, the forward and the
+// kPairMfmaMinRhs right-hand sides on (FP32), and for the split-BF16x3 products
+// always, the matrix cores take 64 right-hand sides per pass, the forward and the
 // backward products as two launches over the blocks (the backward one reads the
-// blocks row-wise through LDS).
+// blocks row-wise through LDS).  FP64 products take the matrix cores from
+// kPairDualMinRhs on, both directions in one pass of 16 or 32 right-hand sides, or
+// 64 in two launches.
 #include <algorithm>
 #include <type_traits>
 
@@ -37,46 +39,6 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // Tags of the 16-bit plane storage (kOpsSplit, kOpsHi).
 struct OpsSplit {};
 struct OpsHi {};
-
-// VEC consecutive stored values from element idx, as FP32.  Planes: the FP32 bit
-// pattern is (hi << 16) + lo, lo the signed remainder (zero for kOpsHi).
-template <typename TS, int VEC>
-__device__ __forceinline__ void load_vals(const PairStream& g, size_t idx, float (&o)[VEC])
-{
-    if constexpr (std::is_same<TS, float>::value) {
-        const float* p = (const float*)g.opsT + idx;
-        if constexpr (VEC == 4) {
-            const v4f v = *(const v4f*)p;
-            o[0] = v[0]; o[1] = v[1]; o[2] = v[2]; o[3] = v[3];
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) o[e] = p[e];
-        }
-    } else {
-        const unsigned short* hp = (const unsigned short*)g.opsT + idx;
-        const short* lp = (const short*)g.opsT_lo + idx;
-        if constexpr (VEC == 4) {
-            const uint2 h = *(const uint2*)hp;
-            const unsigned hv[4] = {h.x & 0xffffu, h.x >> 16, h.y & 0xffffu, h.y >> 16};
-            int lv[4] = {0, 0, 0, 0};
-            if constexpr (std::is_same<TS, OpsSplit>::value) {
-                const uint2 l = *(const uint2*)lp;
-                lv[0] = (short)(l.x & 0xffffu);
-                lv[1] = (short)(l.x >> 16);
-                lv[2] = (short)(l.y & 0xffffu);
-                lv[3] = (short)(l.y >> 16);
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = __uint_as_float((hv[e] << 16) + (unsigned)lv[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-                const int lo = std::is_same<TS, OpsSplit>::value ? (int)lp[e] : 0;
-                o[e] = __uint_as_float(((unsigned)hp[e] << 16) + (unsigned)lo);
-            }
-        }
-    }
-}
 
 // Lane permutations of the DPP butterflies (within rows of 16 lanes).
 constexpr int kDppXor1 = 0xB1;       // quad_perm [1,0,3,2]
@@ -345,33 +307,17 @@ __global__ __launch_bounds__(256) void k_pair_sym(PairStream g, int b0, int R, i
     }
 }
 
-template <int PREC>
-struct Acc;
-template <>
-struct Acc<ERT_FP64> { typedef v4d V; typedef double T; };
-template <>
-struct Acc<ERT_FP32> { typedef v4f V; typedef float T; };
-
-// One stored value as FP32 (element idx).
-template <typename TS>
-__device__ __forceinline__ float load_one(const PairStream& g, size_t idx)
-{
-    float o[1];
-    load_vals<TS, 1>(g, idx, o);
-    return o[0];
-}
-
 // Matrix-core form, 64 right-hand sides per pass: per block, the (M x M) x (M x 64)
 // product of the forward direction (A[r][k] = B[k][r], sources of box b, row
-// fwd_row), FP32 or FP64 accumulation over the FP32 values.  Workgroup: one block
+// fwd_row), in FP32.  Workgroup: one block
 // and 64 RT output rows per wave-row block; the 64 source vectors pass through LDS,
 // 32 reduction indices at a time, transposed so that lanes read consecutive columns;
 // lanes read the block along its rows (consecutive r), coalesced.
-template <int PREC, int RT, typename TS>
+template <int RT>
 __global__ __launch_bounds__(256) void k_pair_mfma(PairStream g, int b0, int rblocks)
 {
-    typedef typename Acc<PREC>::V V;
-    typedef typename Acc<PREC>::T T;
+    typedef v4f V;
+    typedef float T;
     constexpr int KC = 32;
     constexpr int LDW = 80;                       // padded LDS row (columns)
     __shared__ T wsh[KC * LDW];
@@ -383,7 +329,7 @@ __global__ __launch_bounds__(256) void k_pair_mfma(PairStream g, int b0, int rbl
     const int M = g.M;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, grp = lane >> 4, li = lane & 15;
     const int row0 = (rblk * 4 + wave) * 16 * RT;
-    const size_t A = (size_t)p * M * M;
+    const float* ops = (const float*)g.opsT + (size_t)p * M * M;
     V acc[RT][4];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
@@ -405,7 +351,7 @@ __global__ __launch_bounds__(256) void k_pair_mfma(PairStream g, int b0, int rbl
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
                 const int r = row0 + 16 * rt + li;
-                av[rt] = (k < M && r < M) ? (T)load_one<TS>(g, A + (size_t)k * M + r) : T(0);
+                av[rt] = (k < M && r < M) ? ops[(size_t)k * M + r] : T(0);
             }
             T bf[4];
 #pragma unroll
@@ -414,14 +360,11 @@ __global__ __launch_bounds__(256) void k_pair_mfma(PairStream g, int b0, int rbl
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct) {
-                    if constexpr (PREC == ERT_FP64)
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[rt], bf[ct], acc[rt][ct], 0, 0, 0);
-                    else
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rt], bf[ct], acc[rt][ct], 0, 0, 0);
+                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rt], bf[ct], acc[rt][ct], 0, 0, 0);
                 }
         }
     }
-    // FP32 tiles: rows 4 grp + i; FP64 tiles: rows grp + 4 i (column li in both)
+    // rows 4 grp + i of column li
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
         const int b = 16 * ct + li;
@@ -430,102 +373,17 @@ __global__ __launch_bounds__(256) void k_pair_mfma(PairStream g, int b0, int rbl
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             const int base = row0 + 16 * rt;
-            if constexpr (PREC == ERT_FP64) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (base + grp + 4 * i < M) dst[base + grp + 4 * i] = acc[rt][ct][i];
-            } else {
-                if (base + 4 * grp + 3 < M) *(V*)(dst + base + 4 * grp) = acc[rt][ct];
-            }
+            if (base + 4 * grp + 3 < M) *(V*)(dst + base + 4 * grp) = acc[rt][ct];
         }
     }
 }
 
-// The backward direction of the matrix-core form: out[j][b] = sum_i B[j][i] W_a[i][b],
-// whose A operand runs along the stored rows (A[r][k] = B[r][k]).  A tile of the
-// workgroup's 64 RT rows and 32 reduction indices is read row-wise (eight lanes per
-// 128-byte row piece) into LDS, and the lanes take their operands from there.
-template <int PREC, int RT, typename TS>
-__global__ __launch_bounds__(256) void k_pair_mfma_back(PairStream g, int b0, int rblocks)
-{
-    typedef typename Acc<PREC>::V V;
-    typedef typename Acc<PREC>::T T;
-    constexpr int KC = 32;
-    constexpr int LDW = 80;                       // padded LDS row of the sources (columns)
-    constexpr int ROWS = 64 * RT;                 // rows of the workgroup
-    constexpr int TP = KC + 4;                    // tile pitch (floats)
-    __shared__ T wsh[KC * LDW];
-    __shared__ __align__(16) float tile[ROWS * TP];
-    const long p = blockIdx.x / rblocks;
-    const long row = g.bwd_row[p];
-    if (row < 0) return;                          // self block: no backward product (uniform)
-    const int rblk = (int)(blockIdx.x % rblocks);
-    const int nb = (g.B - b0) < 64 ? (g.B - b0) : 64;
-    const int s = g.ua[p];
-    const int M = g.M;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, grp = lane >> 4, li = lane & 15;
-    const int rw0 = rblk * ROWS;                  // first row of the workgroup
-    const int row0 = wave * 16 * RT;              // first row of the wave (in the tile)
-    const size_t A = (size_t)p * M * M;
-    V acc[RT][4];
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = V{0, 0, 0, 0};
-    for (int k0 = 0; k0 < M; k0 += KC) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < 64 * KC; i += 256) {
-            const int b = i / KC, kk = i - b * KC;
-            T v = T(0);
-            if (b < nb && k0 + kk < M) v = ((const T*)g.W)[((long)(b0 + b) * g.nsrc + s) * M + k0 + kk];
-            wsh[kk * LDW + b] = v;
-        }
-        // the tile: ROWS rows x KC columns, 16-byte pieces (M is a multiple of 4)
-        for (int c = threadIdx.x; c < ROWS * (KC / 4); c += 256) {
-            const int rr = c / (KC / 4), c4 = (c - rr * (KC / 4)) * 4;
-            const int r = rw0 + rr, k = k0 + c4;
-            float o[4] = {0.f, 0.f, 0.f, 0.f};
-            if (r < M && k < M) load_vals<TS, 4>(g, A + (size_t)r * M + k, o);
-            *(v4f*)(tile + rr * TP + c4) = v4f{o[0], o[1], o[2], o[3]};
-        }
-        __syncthreads();
-#pragma unroll 2
-        for (int kk = 0; kk < KC; kk += 4) {
-            T av[RT];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) av[rt] = (T)tile[(row0 + 16 * rt + li) * TP + kk + grp];
-            T bf[4];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) bf[ct] = wsh[(kk + grp) * LDW + 16 * ct + li];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    if constexpr (PREC == ERT_FP64)
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[rt], bf[ct], acc[rt][ct], 0, 0, 0);
-                    else
-                        acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[rt], bf[ct], acc[rt][ct], 0, 0, 0);
-                }
-        }
-    }
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        const int b = 16 * ct + li;
-        if (b >= nb) continue;
-        T* dst = (T*)g.stage + ((long)b * g.nrows + row) * M;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int base = rw0 + row0 + 16 * rt;
-            if constexpr (PREC == ERT_FP64) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (base + grp + 4 * i < M) dst[base + grp + 4 * i] = acc[rt][ct][i];
-            } else {
-                if (base + 4 * grp + 3 < M) *(V*)(dst + base + 4 * grp) = acc[rt][ct];
-            }
-        }
-    }
-}
+template <int PREC>
+struct Acc;
+template <>
+struct Acc<ERT_FP64> { typedef v4d V; typedef double T; };
+template <>
+struct Acc<ERT_FP32> { typedef v4f V; typedef float T; };
 
 // Matrix-core form with both operands staged in LDS and the next chunk in flight:
 // per reduction chunk of KC = 32 (FP64: 16) indices the workgroup holds the 64 source
@@ -693,100 +551,197 @@ __global__ __launch_bounds__(256) void k_pair_mma(PairStream g, int b0, int rblo
     }
 }
 
-// Split-BF16x3 form of the same products (FP32-stored blocks, FP32 vectors): every
-// block value a and source value w is split into BF16 parts (hi = bf16(v), lo =
-// bf16(v - hi)) and a w is taken as hi_a hi_w + hi_a lo_w + lo_a hi_w, three
-// 16x16x32 BF16 products accumulated in FP32 (the dropped lo_a lo_w is below
-// 2^-16 |a w|).  The 64 source vectors of a 32-long reduction chunk are split
-// once into LDS, source-major, so that a lane reads its eight reduction indices as
-// one 16-byte vector; each lane loads its eight block values along the reduction
-// (the backward direction reads them contiguously) and splits them in registers.
-template <int RT, bool TRANS>
-__global__ __launch_bounds__(256) void k_pair_mfma_bf16x3(PairStream g, int b0, int rblocks)
+// FP64 products on the matrix cores, both directions of a block in one pass over it,
+// 16 CT right-hand sides (CT 1 or 2).  Workgroup = one stored block, NW waves; wave w
+// owns the 16 TPW columns i of the block from 16 TPW w on.  The block goes by in chunks
+// of 16 stored rows j, staged in LDS as FP32 (two buffers; the next chunk is loaded into
+// registers through a buffer resource spanning the block, rows and columns outside
+// it read as zero, while this one is multiplied).  Per chunk and wave, with D = 16
+// right-hand sides x 16 box indices (so that the stores run along the box index):
+//   forward   F[b][i] += sum_j w_b[j] B[j][i]   over the chunk's rows, i the wave's columns:
+//             accumulators kept for the whole block, sources of box b loaded per chunk;
+//   backward  G[b][j] = sum_i w_a[i] B[j][i]    over the wave's columns: the waves' parts
+//             meet in LDS and are added in wave order, and the chunk's rows are final;
+//             the wave's sources of box a stay in registers.
+// Bound: the FP64 matrix pipe (64 cycles per 16x16x4 product, two per 64 stored values
+// and 16 right-hand sides) and, at CT = 1, HBM about equally.  With one launch per
+// direction and 64 columns per pass (the form used from 16 columns on before) a block is
+// read twice, and few columns pay for 64; the streaming form takes 4 columns per pass.
+// 45 x 38 x 51, order 6: 3 columns 1.47 ms (streamed 1.67), 12 columns 1.64 ms (4.37), 32
+// columns 3.20 ms (5.21 with 64-column tiles).
+template <int NW, int TPW, int CT, typename TS>
+__global__ __launch_bounds__(64 * NW, (CT == 1 && TPW <= 2) ? 4 : 2) void k_pair_dual(PairStream g, int b0, int nb)
 {
-    constexpr int KC = 32;
-    constexpr int LDK = KC + 8;                   // padded LDS row (reduction indices)
-    __shared__ __bf16 whi[64 * LDK];
-    __shared__ __bf16 wlo[64 * LDK];
-    const long p = blockIdx.x / rblocks;
-    const long row = TRANS ? g.bwd_row[p] : g.fwd_row[p];
-    if (row < 0) return;                          // self block: no backward product (uniform)
-    const int rblk = (int)(blockIdx.x % rblocks);
-    const int nb = (g.B - b0) < 64 ? (g.B - b0) : 64;
-    const int s = TRANS ? g.ua[p] : g.ub[p];
+    constexpr bool SPLIT = std::is_same<TS, OpsSplit>::value;
+    constexpr int ESZ = SPLIT ? 2 : 4;
+    constexpr int KC = 16;
+    constexpr int COLS = 16 * TPW * NW;           // block columns the waves cover
+    constexpr int P = COLS + 4;                   // LDS pitch of a stored row
+    constexpr int NT = 64 * NW;
+    constexpr int PR = COLS / 4;                  // 4-value pieces per row
+    static_assert(KC * PR == TPW * NT, "TPW pieces per thread");
+    __shared__ __align__(16) float tile[2][KC * P];
+    __shared__ double part[2][NW * CT * 256];
+    constexpr int WP = 16 * CT + 2;               // LDS pitch of the sources of box b, [j][right-hand side]
+    __shared__ double wsh[2][KC * WP];
+    constexpr int NWB = (KC * 16 * CT + NT - 1) / NT;
+    const long u = blockIdx.x;
+    const int a = g.ua[u], bs = g.ub[u];
+    const long frow = g.fwd_row[u], brow = g.bwd_row[u];
+    const bool back = brow >= 0;                  // uniform
     const int M = g.M;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, grp = lane >> 4, li = lane & 15;
-    const int row0 = (rblk * 4 + wave) * 16 * RT;
-    const size_t A = (size_t)p * M * M;
-    const float* ops = (const float*)g.opsT;
-    v4f acc[RT][4];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, grp = lane >> 4, li = lane & 15;
+    const int i0w = wave * 16 * TPW;
+    const size_t base = (size_t)u * M * M;
+    const unsigned nbytes = (unsigned)((size_t)M * M * ESZ);
+    const __amdgpu_buffer_rsrc_t rs0 = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const unsigned char*)g.opsT + base * ESZ), 0, (int)nbytes, kBufFlags);
+    const __amdgpu_buffer_rsrc_t rs1 = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((const unsigned char*)(SPLIT ? g.opsT_lo : g.opsT) + base * ESZ), 0, (int)nbytes, kBufFlags);
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    const double* Wb = (const double*)g.W + ((long)b0 * g.nsrc + bs) * M;
+    const double* Wa = (const double*)g.W + ((long)b0 * g.nsrc + a) * M;
+    const long ws = (long)g.nsrc * M;
+    // registers of a chunk on its way: the thread's pieces of the block and its sources
+    struct Piece {
+        v4u p[TPW];
+        double w[NWB];
+    };
+    auto fetch = [&](int j0, Piece& r) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0, 0, 0, 0};
-    for (int k0 = 0; k0 < M; k0 += KC) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < 64 * KC; i += 256) {
-            const int b = i / KC, kk = i - b * KC;
-            float v = 0.f;
-            if (b < nb && k0 + kk < M) v = ((const float*)g.W)[((long)(b0 + b) * g.nsrc + s) * M + k0 + kk];
-            const __bf16 h = (__bf16)v;
-            whi[b * LDK + kk] = h;
-            wlo[b * LDK + kk] = (__bf16)(v - (float)h);
-        }
-        __syncthreads();
-        v8bf ah[RT], al[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int r = row0 + 16 * rt + li;
-            const int kb = k0 + 8 * grp;
-            float av[8];
-            if (TRANS && r < M && kb + 8 <= M) {
-                const v4f x0 = *(const v4f*)(ops + A + (size_t)r * M + kb);
-                const v4f x1 = *(const v4f*)(ops + A + (size_t)r * M + kb + 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    av[e] = x0[e];
-                    av[4 + e] = x1[e];
-                }
+        for (int q = 0; q < TPW; ++q) {
+            const int e = tid + NT * q, j = j0 + e / PR, i = 4 * (e % PR);
+            const unsigned off = (j < M && i < M) ? (unsigned)((j * M + i) * ESZ) : kBufOob;
+            if constexpr (SPLIT) {
+                const v2u h = __builtin_amdgcn_raw_buffer_load_b64(rs0, off, 0, 0);
+                const v2u l = __builtin_amdgcn_raw_buffer_load_b64(rs1, off, 0, 0);
+                r.p[q] = v4u{h[0], h[1], l[0], l[1]};
             } else {
+                r.p[q] = __builtin_amdgcn_raw_buffer_load_b128(rs0, off, 0, 0);
+            }
+        }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int k = kb + e;
-                    av[e] = (k < M && r < M) ? ops[TRANS ? A + (size_t)r * M + k : A + (size_t)k * M + r] : 0.f;
+        for (int q = 0; q < NWB; ++q) {
+            const int e = tid + NT * q, b = e / KC, j = j0 + e % KC;
+            r.w[q] = (b < nb && j < M) ? Wb[b * ws + j] : 0.0;
+        }
+    };
+    auto stash = [&](int buf, const Piece& r) {
+#pragma unroll
+        for (int q = 0; q < TPW; ++q) {
+            const int e = tid + NT * q;
+            v4u v = r.p[q];
+            if constexpr (SPLIT) {
+                const unsigned h0 = v[0], h1 = v[1];
+                const int l0 = (int)v[2], l1 = (int)v[3];
+                v = v4u{(h0 << 16) + (unsigned)((l0 << 16) >> 16), (h0 & 0xffff0000u) + (unsigned)(l0 >> 16),
+                        (h1 << 16) + (unsigned)((l1 << 16) >> 16), (h1 & 0xffff0000u) + (unsigned)(l1 >> 16)};
+            }
+            *(v4u*)(tile[buf] + (e / PR) * P + 4 * (e % PR)) = v;
+        }
+#pragma unroll
+        for (int q = 0; q < NWB; ++q) {
+            const int e = tid + NT * q;
+            if (e < KC * 16 * CT) wsh[buf][(e % KC) * WP + e / KC] = r.w[q];
+        }
+    };
+    constexpr bool DEEP = CT == 1;                // two chunks on their way (with CT 2 they would spill)
+    Piece ra, rb;
+    fetch(0, ra);
+    // the wave's sources of box a: right-hand side 16 c + li, column 16 t + 4 s + grp
+    double wa[TPW][CT][4];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int i = i0w + 16 * t + 4 * s + grp, b = 16 * c + li;
+                wa[t][c][s] = (back && b < nb && i < M) ? Wa[b * ws + i] : 0.0;
+            }
+    v4d acc[TPW][CT];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[t][c] = v4d{0, 0, 0, 0};
+    stash(0, ra);
+    if constexpr (DEEP) fetch(KC, ra);
+    __syncthreads();
+    double* stage = (double*)g.stage;
+    // chunk j0 from LDS buffer cur; `next` holds chunk j0 + KC (in flight; or receives it
+    // now), `after` receives chunk j0 + 2 KC
+    auto step = [&](int j0, int cur, Piece& next, Piece& after) {
+        if constexpr (DEEP) fetch(j0 + 2 * KC, after);
+        else fetch(j0 + KC, next);
+        const float* T = tile[cur];
+        double w[CT][4];
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) w[c][s] = wsh[cur][(4 * s + grp) * WP + 16 * c + li];
+        v4d bk[CT][2];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) bk[c][0] = bk[c][1] = v4d{0, 0, 0, 0};
+#pragma unroll
+        for (int t = 0; t < TPW; ++t) {
+            const float* Tf = T + grp * P + i0w + 16 * t + li;       // forward: rows 4 s + grp
+            const float* Tb = T + li * P + i0w + 16 * t + grp;       // backward: row li
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double xf = (double)Tf[4 * s * P];
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    acc[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[c][s], xf, acc[t][c], 0, 0, 0);
+                if (back) {
+                    const double xb = (double)Tb[4 * s];
+#pragma unroll
+                    for (int c = 0; c < CT; ++c)
+                        bk[c][s & 1] =
+                            __builtin_amdgcn_mfma_f64_16x16x4f64(wa[t][c][s], xb, bk[c][s & 1], 0, 0, 0);
                 }
             }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const __bf16 h = (__bf16)av[e];
-                ah[rt][e] = h;
-                al[rt][e] = (__bf16)(av[e] - (float)h);
-            }
         }
+        // D: right-hand side grp + 4 i, box index li
+        if (back) {
+            double* pw = part[cur] + wave * CT * 256;
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            const int b = 16 * ct + li;
-            const v8bf bh = *(const v8bf*)(whi + b * LDK + 8 * grp);
-            const v8bf bl = *(const v8bf*)(wlo + b * LDK + 8 * grp);
+            for (int c = 0; c < CT; ++c)
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[rt], bh, acc[rt][ct], 0, 0, 0);
-                acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[rt], bl, acc[rt][ct], 0, 0, 0);
-                acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[rt], bh, acc[rt][ct], 0, 0, 0);
-            }
+                for (int i = 0; i < 4; ++i) pw[c * 256 + i * 64 + lane] = bk[c][0][i] + bk[c][1][i];
         }
+        stash(cur ^ 1, next);
+        __syncthreads();
+        if (back)
+            for (int e = tid; e < CT * 256; e += NT) {
+                const double* q = part[cur] + e;
+                double s = q[0];
+#pragma unroll
+                for (int k = 1; k < NW; ++k) s += q[k * CT * 256];
+                const int b = 16 * (e >> 8) + 4 * ((e >> 6) & 3) + ((e & 63) >> 4), j = j0 + (e & 15);
+                if (b < nb && j < M) stage[((long)b * g.nrows + brow) * M + j] = s;
+            }
+    };
+    if constexpr (DEEP) {
+        for (int j0 = 0; j0 < M; j0 += 2 * KC) {
+            step(j0, 0, ra, rb);
+            if (j0 + KC >= M) break;              // uniform
+            step(j0 + KC, 1, rb, ra);
+        }
+    } else {
+        for (int j0 = 0, cur = 0; j0 < M; j0 += KC, cur ^= 1) step(j0, cur, ra, ra);
     }
-    // rows 4 grp + i of column li
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        const int b = 16 * ct + li;
-        if (b >= nb) continue;
-        float* dst = (float*)g.stage + ((long)b * g.nrows + row) * M;
+    for (int t = 0; t < TPW; ++t) {
+        const int i = i0w + 16 * t + li;
+        if (i >= M) continue;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int base = row0 + 16 * rt;
-            if (base + 4 * grp + 3 < M) *(v4f*)(dst + base + 4 * grp) = acc[rt][ct];
-        }
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int b = 16 * c + grp + 4 * k;
+                if (b < nb) stage[((long)b * g.nrows + frow) * M + i] = acc[t][c][k];
+            }
     }
 }
 
@@ -1060,44 +1015,83 @@ ert_status pair_sym_t(hipStream_t s, const PairStream& g, const PairGen* gen)
     return ERT_OK;
 }
 
-// Matrix-core form (FP32 storage, whole or in planes), 64 right-hand sides per pass.
-template <int PREC, typename TS>
+// FP32 matrix-core form (whole storage or planes), 64 right-hand sides per pass; M a
+// multiple of 4.
+template <typename TS>
 ert_status pair_mfma_t(hipStream_t s, const PairStream& g, const PairGen* gen)
 {
-    constexpr int RT = (PREC == ERT_FP64) ? 4 : 8;
-    constexpr int RTB = 4;                        // backward: 256 rows per workgroup (LDS tile)
-    typedef typename Acc<PREC>::T T;
+    constexpr int RT = 8;
+    constexpr int RTB = 4;                        // staged form: 256 rows per workgroup (LDS tile)
     const int rblocks = (g.M + 64 * RT - 1) / (64 * RT);
     const int rblocksb = (g.M + 64 * RTB - 1) / (64 * RTB);
-    for (int b0 = 0; b0 < g.B; b0 += 64) {
-        const int nb = std::min(64, g.B - b0);
+    for (int b0 = 0; b0 < g.B; b0 += kPairMfmaRhs) {
+        const int nb = std::min(kPairMfmaRhs, g.B - b0);
         StageTimer t_(g.prof, s, g.prof_stage);
         ERT_TRY(for_each_chunk(s, g, gen, [&](const PairStream& c) -> ert_status {
             const dim3 grid((unsigned)(c.npairs * rblocks)), gridb((unsigned)(c.npairs * rblocksb));
-            // whole 4-value pieces of the stored rows: both operands staged in LDS, the
-            // next chunk in flight (the FP32 forward product over FP32-stored blocks keeps its
-            // 512-row tiles, whose operators come straight from memory: it keeps the matrix
-            // cores about 60 % busy already)
-            const bool piecewise = c.M % 4 == 0;
-            bool fwd_done = false;
-            if constexpr (PREC == ERT_FP64 || !std::is_same<TS, float>::value) {
-                // FP64, or values in 16-bit planes (decoded once into the LDS tile)
-                if (piecewise) {
-                    hipLaunchKernelGGL((k_pair_mma<PREC, RTB, TS, false>), gridb, dim3(256), 0, s, c, b0, rblocksb);
-                    fwd_done = true;
-                }
-            }
-            if (!fwd_done) hipLaunchKernelGGL((k_pair_mfma<PREC, RT, TS>), grid, dim3(256), 0, s, c, b0, rblocks);
-            ERT_HIP(hipGetLastError());
-            if (piecewise)
-                hipLaunchKernelGGL((k_pair_mma<PREC, RTB, TS, true>), gridb, dim3(256), 0, s, c, b0, rblocksb);
+            // both operands staged in LDS, the next chunk in flight (the forward product over
+            // FP32-stored blocks keeps its 512-row tiles, whose operators come straight from
+            // memory: it keeps the matrix cores about 60 % busy already; values in 16-bit
+            // planes are decoded once into the LDS tile)
+            if constexpr (std::is_same<TS, float>::value)
+                hipLaunchKernelGGL((k_pair_mfma<RT>), grid, dim3(256), 0, s, c, b0, rblocks);
             else
-                hipLaunchKernelGGL((k_pair_mfma_back<PREC, RTB, TS>), gridb, dim3(256), 0, s, c, b0, rblocksb);
+                hipLaunchKernelGGL((k_pair_mma<ERT_FP32, RTB, TS, false>), gridb, dim3(256), 0, s, c, b0, rblocksb);
+            ERT_HIP(hipGetLastError());
+            hipLaunchKernelGGL((k_pair_mma<ERT_FP32, RTB, TS, true>), gridb, dim3(256), 0, s, c, b0, rblocksb);
             ERT_HIP(hipGetLastError());
             return ERT_OK;
         }));
         t_.stop();
-        ERT_TRY(launch_reduce<T>(s, g, b0, nb));
+        ERT_TRY(launch_reduce<float>(s, g, b0, nb));
+    }
+    return ERT_OK;
+}
+
+template <int CT, typename TS>
+void launch_dual(hipStream_t s, const PairStream& g, int b0, int nb)
+{
+    const dim3 grid((unsigned)g.npairs);
+    // waves of 16 TPW columns: four for up to 64 columns, else eight with the fewest tiles that cover M
+    if (g.M <= 64) hipLaunchKernelGGL((k_pair_dual<4, 1, CT, TS>), grid, dim3(256), 0, s, g, b0, nb);
+    else if (g.M <= 128) hipLaunchKernelGGL((k_pair_dual<8, 1, CT, TS>), grid, dim3(512), 0, s, g, b0, nb);
+    else if (g.M <= 256) hipLaunchKernelGGL((k_pair_dual<8, 2, CT, TS>), grid, dim3(512), 0, s, g, b0, nb);
+    else if (g.M <= 384) hipLaunchKernelGGL((k_pair_dual<8, 3, CT, TS>), grid, dim3(512), 0, s, g, b0, nb);
+    else hipLaunchKernelGGL((k_pair_dual<8, 4, CT, TS>), grid, dim3(512), 0, s, g, b0, nb);
+}
+
+// FP64 matrix-core forms, M a multiple of 4 up to 512: passes of 64 right-hand sides where
+// pair_pass64 says so (the two directions apart), else both directions in one pass of 32
+// while more than 16 are left, then of 16.
+template <typename TS>
+ert_status pair_dual_t(hipStream_t s, const PairStream& g, const PairGen* gen)
+{
+    constexpr int RTB = 4;
+    if (g.M > 512) {
+        record_error("pair_stream: unsupported block size");
+        return ERT_EINVAL;
+    }
+    const int rblocks = (g.M + 64 * RTB - 1) / (64 * RTB);
+    for (int b0 = 0, nb = 0; b0 < g.B; b0 += nb) {
+        const bool wide = pair_pass64(g.M, std::min<int>(g.B - b0, (int)g.rows));
+        nb = std::min(std::min(wide ? kPairMfmaRhs : kPairDualRhs, (int)g.rows), g.B - b0);
+        {
+            StageTimer t_(g.prof, s, g.prof_stage);
+            ERT_TRY(for_each_chunk(s, g, gen, [&](const PairStream& c) -> ert_status {
+                if (wide) {
+                    const dim3 grid((unsigned)(c.npairs * rblocks));
+                    hipLaunchKernelGGL((k_pair_mma<ERT_FP64, RTB, TS, false>), grid, dim3(256), 0, s, c, b0, rblocks);
+                    hipLaunchKernelGGL((k_pair_mma<ERT_FP64, RTB, TS, true>), grid, dim3(256), 0, s, c, b0, rblocks);
+                } else if (nb > 16) {
+                    launch_dual<2, TS>(s, c, b0, nb);
+                } else {
+                    launch_dual<1, TS>(s, c, b0, nb);
+                }
+                ERT_HIP(hipGetLastError());
+                return ERT_OK;
+            }));
+        }
+        ERT_TRY(launch_reduce<double>(s, g, b0, nb));
     }
     return ERT_OK;
 }
@@ -1118,15 +1112,9 @@ ert_status pair_mfma_bf16x3(hipStream_t s, const PairStream& g, const PairGen* g
             StageTimer t_(g.prof, s, g.prof_stage);
             ERT_TRY(for_each_chunk(s, g, gen, [&](const PairStream& c) -> ert_status {
                 const dim3 grid((unsigned)(c.npairs * rblocks));
-                if (c.M % 4 == 0) {           // whole 4-value pieces: LDS-staged, next chunk in flight
-                    hipLaunchKernelGGL((k_pair_b3<RT, false>), grid, dim3(256), 0, s, c, b0, rblocks);
-                    ERT_HIP(hipGetLastError());
-                    hipLaunchKernelGGL((k_pair_b3<RT, true>), grid, dim3(256), 0, s, c, b0, rblocks);
-                } else {
-                    hipLaunchKernelGGL((k_pair_mfma_bf16x3<RT, false>), grid, dim3(256), 0, s, c, b0, rblocks);
-                    ERT_HIP(hipGetLastError());
-                    hipLaunchKernelGGL((k_pair_mfma_bf16x3<RT, true>), grid, dim3(256), 0, s, c, b0, rblocks);
-                }
+                hipLaunchKernelGGL((k_pair_b3<RT, false>), grid, dim3(256), 0, s, c, b0, rblocks);
+                ERT_HIP(hipGetLastError());
+                hipLaunchKernelGGL((k_pair_b3<RT, true>), grid, dim3(256), 0, s, c, b0, rblocks);
                 ERT_HIP(hipGetLastError());
                 return ERT_OK;
             }));
@@ -1157,12 +1145,13 @@ ert_status pair_stream(hipStream_t s, int prec, const PairStream& g, const PairG
         }
         return pair_mfma_bf16x3(s, g, gen);
     }
-    if (g.B >= kPairMfmaMinRhs && g.M % 4 == 0) {
+    if (f64 && g.B >= kPairDualMinRhs && g.M % 4 == 0)
+        return g.ops_fmt == kOpsSplit ? pair_dual_t<OpsSplit>(s, g, gen) : pair_dual_t<float>(s, g, gen);
+    if (!f64 && g.B >= kPairMfmaMinRhs && g.M % 4 == 0) {
         switch (g.ops_fmt) {
-        case kOpsSplit:
-            return f64 ? pair_mfma_t<ERT_FP64, OpsSplit>(s, g, gen) : pair_mfma_t<ERT_FP32, OpsSplit>(s, g, gen);
-        case kOpsHi: return pair_mfma_t<ERT_FP32, OpsHi>(s, g, gen);
-        default: return f64 ? pair_mfma_t<ERT_FP64, float>(s, g, gen) : pair_mfma_t<ERT_FP32, float>(s, g, gen);
+        case kOpsSplit: return pair_mfma_t<OpsSplit>(s, g, gen);
+        case kOpsHi: return pair_mfma_t<OpsHi>(s, g, gen);
+        default: return pair_mfma_t<float>(s, g, gen);
         }
     }
     switch (g.ops_fmt) {
