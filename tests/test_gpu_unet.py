@@ -148,6 +148,47 @@ def test_gradient_matches_reference(ev, n, B):
     assert o == g.size
 
 
+# tiles of 8 x 4 x 4 and 8 x 4 x 2 voxels with remainders on every axis and at every level, one
+# tile and several per slab, and other widths (up to 256 input channels: the untiled form)
+@pytest.mark.parametrize("n,B,widths,grad", [((4, 4, 4), 1, WIDTHS, True), ((12, 20, 28), 3, WIDTHS, True),
+                                             ((44, 36, 24), 2, WIDTHS, True), ((8, 4, 36), 1, (32, 16, 48), True),
+                                             ((16, 12, 8), 2, (64, 128, 128), False)])
+def test_tiled_layers_match_reference(ev, n, B, widths, grad):
+    """Weights a tenth of their usual size and biases of 50 keep every unit active: a unit
+    near zero whose mask differs from the float64 reference's would alone change a coarse
+    layer's gradient by one part in the root of its units (7e-3 at 3 x 5 x 7 x 64 x 3)."""
+    import torch
+    r, e, st, ss = _rand(n, B, 14)
+    layers = U.unpack(0.1 * _params(15, widths).astype(np.float64), widths)
+    for W, b in layers:
+        b[...] = 50.0
+    p = U.pack(layers).astype(np.float32)
+    X, S = _oracle_inputs(r, st, ss, n)
+    with ev.Net(n, batch_max=B, widths=widths) as net:
+        net.set_params(p)
+        z = torch.empty((B, int(np.prod(n))), dtype=torch.float64, device="cuda")
+        net.forward(_dev(r), _dev(st), _dev(ss), z)
+        zg = _host(z)
+        loss, g = net.grad(_dev(r), _dev(e), _dev(st), _dev(ss)) if grad else (None, None)
+        if grad:
+            _, g2 = net.grad(_dev(r), _dev(e), _dev(st), _dev(ss))
+            assert np.array_equal(g, g2)                # deterministic
+    Y = U.forward(p.astype(np.float64), X, widths, bf16=True)
+    assert rel_l2(zg - r, Y.reshape(B, -1) * S[:, None]) <= 1e-4
+    if not grad:
+        return
+    T = np.stack([U.target(r[b], e[b]).astype(np.float32).astype(np.float64).reshape(n[2], n[1], n[0])
+                  for b in range(B)])
+    Lr, gr = U.loss_and_grad(p.astype(np.float64), X, T, widths, bf16=True)
+    assert abs(loss - Lr) <= 1e-4 * abs(Lr)
+    o = 0
+    for li, (co, ci, k) in enumerate(U.layer_shapes(widths)):
+        nw = co * ci * k ** 3
+        for name, a, b in (("W", o, o + nw), ("b", o + nw, o + nw + co)):
+            assert rel_l2(g[a:b].astype(np.float64), gr[a:b]) <= 1e-3, (li + 1, name)
+        o += nw + co
+
+
 def test_adam_step_matches_reference(ev):
     n, B = (8, 8, 8), 2
     r, e, st, ss = _rand(n, B, 6)
