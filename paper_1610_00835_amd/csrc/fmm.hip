@@ -81,15 +81,6 @@ __device__ __forceinline__ long slot_cell(const DevTree& t, long slot, int c[3])
 
 // ---------------------------------------------------- gather / assemble ----
 
-// Vectors and operator of the current apply, read by the first and last kernel
-// so that one captured graph serves every call with the same rhs count.
-struct ApplyIO {
-    const double* x;
-    double* y;
-    int op;
-    int pad;
-};
-
 // The first kernel of an apply receives the apply's vectors as an argument (the
 // argument of a replayed graph's root node is updated per call) and stores them
 // for the later kernels of the apply, which read them through io.
@@ -1412,6 +1403,9 @@ struct FmmImpl : FmmData {
     T* leaf_out = nullptr;              // [S][rp] = P^T Um
     T* leaf_inT = nullptr;              // [S][rp], leaf_in transposed
     T* leaf_outT = nullptr;             // [rp][S], leaf_out transposed
+    bool fast2d = false;                // FP64 2D homogeneous apply in a few launches (hom2d.hip)
+    double* far2d[kMaxLevels + 1] = {}; // its matrices in fragment order
+    double* near2d = nullptr;
     HetCache* hc = nullptr;             // heterogeneous caches (owned by the plan)
     T* nearops = nullptr;               // homogeneous near blocks [3^d][S][S]
     T* neartab = nullptr;               // the same values over cell offsets, [4][near_tlen]
@@ -1437,12 +1431,13 @@ struct FmmImpl : FmmData {
         ApplyIO a; ApplyIO* io; DevTree t; const double* ss; long N; const T* linT; int R; int rch; T* q; T* W;
     };
     struct FirstLaunch {
-        int kind = 0;                   // 1 k_gather, 2 k_leaf_in
+        int kind = 0;                   // 1 k_gather, 2 k_leaf_in, 3 hom2d_first_kernel
         const void* func = nullptr;
         dim3 grid, block;
         size_t shmem = 0;
         GatherArgs g{};
         LeafInArgs l{};
+        Hom2dUp u{};
     };
     FirstLaunch first;                  // of the most recent enqueue
     FirstLaunch gfirst[2];              // of the captured applies
@@ -1480,8 +1475,10 @@ struct FmmImpl : FmmData {
         for (int l = 0; l <= kMaxLevels; ++l) {
             f(ops[l]); f(ops_lo[l]); f(Ut[l]); f(Um[l]);
             f(W[l]); f(Lc[l]); f(Wc[l]); f(Lh[l]);
+            f(far2d[l]);
             far_site[l].release();
         }
+        f(near2d);
         near_site.release();
         f(stage); f(stage_near); f(tune); f(io);
         drop_graphs();
@@ -1523,6 +1520,7 @@ struct FmmImpl : FmmData {
     }
     ert_status enqueue_grouped(ert_plan_impl* p, hipStream_t s, int nrhs);
     ert_status set_root_args(int bucket);
+    ert_status enqueue_2d(ert_plan_impl* p, hipStream_t s, int nrhs);
     ert_status enqueue(ert_plan_impl* p, hipStream_t s, int nrhs);
     void drop_graphs()
     {
@@ -1551,6 +1549,14 @@ struct FmmImpl : FmmData {
     }
     ert_status setup(ert_plan_impl* p) override;
     ert_status setup_far_hom(ert_plan_impl* p, int l, double svd_tol);
+    // translation matrices of level l (Kp x Kp each, device) into fragment order; drains the stream
+    ert_status pack_far2d(hipStream_t s, int l, const double* M, int nmat)
+    {
+        ERT_HIP(hipMalloc(&far2d[l], (size_t)nmat * hom2d_fragment_elems(tr.K) * sizeof(double)));
+        ERT_TRY(hom2d_fragments(s, M, tr.Kp, tr.K, nmat, far2d[l]));
+        ERT_HIP(hipStreamSynchronize(s));
+        return ERT_OK;
+    }
     ert_status setup_het(ert_plan_impl* p);
     ert_status ensure_buffers(int nrhs);
     hipStream_t p_stream = nullptr;
@@ -1664,13 +1670,24 @@ ert_status FmmImpl<T>::setup_far_hom(ert_plan_impl* p, int l, double svd_tol)
         ERT_TRY(gemm_bt(s, g1));
         GemmBT g2{R, R, Kp, noff, 0, U64, 0, 1, R, T1, (long)Kp * R, 1, R, C64, (long)R * R, R, 1};
         ERT_TRY(gemm_bt(s, g2));
+        rp[l] = R;
+        if (fast2d) {
+            // the same map as full matrices, U C_o U^T
+            double *X = nullptr, *F = nullptr;
+            ERT_TRY(tmp.alloc(&X, (size_t)noff * Kp * R));
+            ERT_TRY(tmp.alloc(&F, (size_t)noff * KpKp));
+            GemmBT g3{Kp, R, R, noff, 0, U64, 0, R, 1, C64, (long)R * R, 1, R, X, (long)Kp * R, R, 1};
+            ERT_TRY(gemm_bt(s, g3));
+            GemmBT g4{Kp, Kp, R, noff, 0, X, (long)Kp * R, R, 1, U64, 0, R, 1, F, KpKp, Kp, 1};
+            ERT_TRY(gemm_bt(s, g4));
+            return pack_far2d(s, l, F, noff);
+        }
         // change-of-basis matrices in the working precision
         std::vector<double> Ut_h((size_t)R * Kp);
         for (int c = 0; c < R; ++c)
             for (int i = 0; i < Kp; ++i) Ut_h[(size_t)c * Kp + i] = Uh[(size_t)i * R + c];
         ERT_TRY(upload_cvt<T>(s, &Ut[l], Ut_h));
         ERT_TRY(upload_cvt<T>(s, &Um[l], Uh));
-        rp[l] = R;
         if (l == 2 && tr.L == 2 && tr.S % 32 == 0) {
             // dense leaf interpolation P[m][j] = prod_a S_n(x_{j_a}, node_{m_a}) (the separable
             // P2M/L2P operator), folded with the basis change
@@ -1724,6 +1741,7 @@ ert_status FmmImpl<T>::setup_far_hom(ert_plan_impl* p, int l, double svd_tol)
         Cd = C64;
         M = R;
     }
+    if (fast2d) return pack_far2d(s, l, M64, noff);
     const long n = (long)noff * M * M;
     if (prec == ERT_BF16X3) {
         ERT_HIP(hipMalloc(&ops[l], n * sizeof(__bf16)));
@@ -2159,7 +2177,21 @@ ert_status FmmImpl<T>::setup(ert_plan_impl* p)
 
     if (!hetero) {
         const double sigma = p->sigma_const, h = p->geo.h;
-        if (tr.S % 32 == 0) {
+        // FP64 in 2D with the default leaves and no form asked for (FP32 sums keep the order of
+        // the general path, whose rounding is part of their result)
+        fast2d = prec == ERT_FP64 && tr.D == 2 && leaf == 8 && tr.L >= 2 && p->o.form[0] == 0 && p->o.form[1] == 0;
+        if (fast2d) {
+            DevPtrs tmp;
+            double* blk = nullptr;
+            const long n = 9L * tr.S * tr.S;
+            ERT_TRY(tmp.alloc(&blk, (size_t)n));
+            hipLaunchKernelGGL(k_near_ops<double>, dim3(blocks(n)), dim3(kB), 0, s, tr.D, leaf, tr.S, h, sigma, blk,
+                               p->o.scheme);
+            ERT_HIP(hipGetLastError());
+            ERT_HIP(hipMalloc(&near2d, 9 * hom2d_fragment_elems(tr.S) * sizeof(double)));
+            ERT_TRY(hom2d_fragments(s, blk, tr.S, tr.S, 9, near2d));
+            ERT_HIP(hipStreamSynchronize(s));   // blk is freed here
+        } else if (tr.S % 32 == 0) {
             const int nn = tr.D == 3 ? 27 : 9;
             const long n = (long)nn * tr.S * tr.S;
             ERT_HIP(hipMalloc(&nearops, n * sizeof(T)));
@@ -2196,7 +2228,7 @@ ert_status FmmImpl<T>::setup(ert_plan_impl* p)
         for (int l = 2; l <= tr.L; ++l) ERT_TRY(setup_far_hom(p, l, svd_tol));
         // both execution forms of the box-offset products
         if (nearops) ERT_TRY(build_site(s, tr.D, tr.nl[tr.L], false, near_site));
-        for (int l = 2; l <= tr.L; ++l) ERT_TRY(build_site(s, tr.D, tr.nl[l], true, far_site[l]));
+        for (int l = 2; l <= tr.L && !fast2d; ++l) ERT_TRY(build_site(s, tr.D, tr.nl[l], true, far_site[l]));
     } else {
         ERT_TRY(setup_het(p));
     }
@@ -2227,7 +2259,7 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
         // node padding (K..Kp) stays zero: the transfers never write it
         ERT_HIP(hipMemset(W[l], 0, n * sizeof(T)));
         ERT_HIP(hipMemset(Lc[l], 0, n * sizeof(T)));
-        if (rp[l] > 0) {
+        if (rp[l] > 0 && !fast2d) {
             size_t m = (size_t)nrhs * tr.nbox[l] * rp[l];
             ERT_HIP(hipMalloc(&Wc[l], m * sizeof(T)));
             ERT_HIP(hipMalloc(&Lh[l], m * sizeof(T)));
@@ -2400,9 +2432,52 @@ ert_status FmmImpl<T>::enqueue_grouped(ert_plan_impl* p, hipStream_t s, int nrhs
     return ERT_OK;
 }
 
+// The whole apply of an FP64 homogeneous 2D plan (hom2d.hip).
+template <typename T>
+ert_status FmmImpl<T>::enqueue_2d(ert_plan_impl* p, hipStream_t s, int nrhs)
+{
+    if constexpr (std::is_same<T, double>::value) {
+        Hom2d t{};
+        t.nc = tr.nc; t.K = tr.K; t.ld = tr.Kp; t.L = tr.L;
+        t.n0 = p->geo.n0; t.n1 = p->geo.n1;
+        t.N = p->N;
+        Hom2dProducts pr{};
+        for (int l = 0; l <= tr.L; ++l) {
+            t.nl0[l] = tr.nl[l][0];
+            t.nl1[l] = tr.nl[l][1];
+            t.W[l] = W[l];
+            t.Lc[l] = Lc[l];
+            pr.far[l] = far2d[l];
+        }
+        t.q = q; t.pot = pot; t.P1 = P1; t.M1 = M1;
+        pr.t = t;
+        pr.near = near2d;
+        pr.far_offs = m2l_offs;
+        pr.near_offs = near_offs;
+        {
+            StageTimer st_(&p->prof, s, ERT_STAGE_P2M);
+            first.kind = 3;
+            first.u = Hom2dUp{cur, io, p->d_ss, t, std::max(2, tr.L - 2), tr.L};
+            first.func = hom2d_first_kernel();
+            first.grid = hom2d_up_grid(first.u, nrhs);
+            first.block = hom2d_up_block(first.u);
+            first.shmem = 0;
+            ERT_TRY(hom2d_up(s, first.u, nrhs));
+        }
+        {
+            StageTimer st_(&p->prof, s, ERT_STAGE_M2L);
+            ERT_TRY(hom2d_products(s, pr, nrhs));
+        }
+        StageTimer st_(&p->prof, s, ERT_STAGE_L2P);
+        return hom2d_down(s, Hom2dDown{io, p->d_ss, p->d_diag, std::pow(p->geo.h, tr.D), t, 0, 0}, nrhs);
+    }
+    return ERT_EINVAL;
+}
+
 template <typename T>
 ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
 {
+    if (fast2d) return enqueue_2d(p, s, nrhs);
     {
         const int bk = nrhs > 1 ? 1 : 0;
         if (grouped_form(bk)) return enqueue_grouped(p, s, nrhs);
@@ -2730,6 +2805,11 @@ ert_status FmmImpl<T>::set_root_args(int bucket)
         GatherArgs& A = f.g;
         A.a = cur;
         void* args[] = {&A.a, &A.io, &A.t, &A.ss, &A.N, &A.B, &A.q};
+        kp.kernelParams = args;
+        ERT_HIP(hipGraphExecKernelNodeSetParams(gexec[bucket], groot[bucket], &kp));
+    } else if (f.kind == 3) {
+        f.u.a = cur;
+        void* args[] = {&f.u};
         kp.kernelParams = args;
         ERT_HIP(hipGraphExecKernelNodeSetParams(gexec[bucket], groot[bucket], &kp));
     } else {

@@ -138,6 +138,65 @@ ert_status offset_gemm_reduce(hipStream_t s, int prec, const OffsetGemm& g);    
 // (two launches when only one of them is in form 4)
 ert_status offset_gemm_pair_products(hipStream_t s, int prec, const OffsetGemm& a, const OffsetGemm& b);
 
+// Vectors and operator of the current apply, read by the first and last kernel so that one
+// captured graph serves every call with the same rhs count.
+struct ApplyIO {
+    const double* x;
+    double* y;
+    int op;
+    int pad;
+};
+
+// FP64 apply of a homogeneous 2D medium with leaves of 8 x 8 cells (hom2d.hip).
+struct Hom2d {
+    int nc, K, ld, L;                     // nodes per axis and box; entries per box of W and Lc; leaf level (>= 2)
+    int n0, n1;
+    int nl0[kMaxLevels + 1], nl1[kMaxLevels + 1];
+    long N;
+    double* W[kMaxLevels + 1];            // [rhs][box][ld] multipoles (entries past K zero)
+    double* Lc[kMaxLevels + 1];           // [rhs][box][ld] translated locals, then the locals
+    double* q;                            // [rhs][leaf][64] weighted charges
+    double* pot;                          // [rhs][leaf][64] near-field potentials
+    const double* P1;                     // [nc][8]
+    const double* M1;                     // [2][nc][nc]
+};
+struct Hom2dUp {
+    ApplyIO a;
+    ApplyIO* io;
+    const double* ss;
+    Hom2d t;
+    int top, low;
+};
+struct Hom2dDown {
+    const ApplyIO* io;
+    const double* ss;
+    const double* diag;
+    double hd;
+    Hom2d t;
+    int top, low;
+};
+struct Hom2dProducts {
+    Hom2d t;
+    const double* far[kMaxLevels + 1];    // fragments of the 7^2 translation matrices per level
+    const double* near;                   // fragments of the 3^2 near blocks
+    const BoxOffset* far_offs;            // [4 classes][27]
+    const BoxOffset* near_offs;           // [9]
+    int tiles[kMaxLevels + 1];            // column tiles per level (set by hom2d_products)
+    int near_tiles;
+};
+// Values of one K x K matrix in fragment order, and the conversion of nmat row-major matrices
+// (ld x ld each, K used).
+size_t hom2d_fragment_elems(int K);
+ert_status hom2d_fragments(hipStream_t s, const double* src, int ld, int K, long nmat, double* dst);
+// The passes of an apply in their order; `first` is the apply's first launch (top =
+// max(2, L - 2), low = L), with its kernel, grid and block for the root of a captured graph.
+const void* hom2d_first_kernel();
+dim3 hom2d_up_grid(const Hom2dUp& u, int nrhs);
+dim3 hom2d_up_block(const Hom2dUp& u);
+ert_status hom2d_up(hipStream_t s, const Hom2dUp& first, int nrhs);
+ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs);
+ert_status hom2d_down(hipStream_t s, Hom2dDown d, int nrhs);
+
 // Storage of the cached blocks read by the pair products.
 enum {
     kOpsNative = 0,          // values of the arithmetic type (not used by the heterogeneous caches)
