@@ -644,125 +644,265 @@ __global__ void k_corner8(Geo g, const double* __restrict__ st, double* __restri
     q[3] = make_double2(st[b + d2 + d1], st[b + d2 + d1 + d0]);
 }
 
-// Cached near-field blocks for the ray kernel, FP64 arithmetic: the same rule
-// as the dense apply (exact integer step count, marched from the lower index,
-// so the value of a cell pair does not depend on its order).  One workgroup per
-// stored pair u (blocks u0 .. ; blk and lo_plane point at block u0): element
-// [si][ti] = G(cell ti of leaf ua[u], cell si of leaf ub[u]), zero for a cell
-// with itself (the diagonal's term).  FP32 values as a BF16-rounded high plane
-// and the exact remainder.  sigma_t over the cells spanned by the two leaves,
-// plus one layer above (the upper corner of a sample on the top face), is
-// staged in LDS and the march reads it there: samples lie between the two cell
-// centres, so every corner they need is in the box.  Cell search and
-// interpolation are sigma_at's, term for term.  Leaves have at most
-// kNearLdsLeaf cells per side (the plan's limit).
-constexpr int kNearLdsLeaf = 8;
-constexpr int kNearLdsSide = 2 * kNearLdsLeaf + 1;
-constexpr int kNearLdsThreads = 512;
+// Cached near-field blocks for the ray kernel, FP64 arithmetic: the same rule as the dense
+// apply (exact integer step count).  Between two cell centres the samples of the rule and
+// their interpolation weights depend on the integer offset d alone, so the sum of the m
+// samples is a fixed stencil over sigma_t,
+//   sum_q sigma(x + f_q d) = sum_k w_dk sigma[cell + k],
+// about 60 distinct cells for the 25 samples of eight corners each of a near pair in 3D.
+// k_near_taps forms the stencils (rational positions, exact cells; corners of weight zero
+// dropped, so every cell lies in the box spanned by the two ends) of the offsets that
+// follow zero in the order z, y, x; the opposite offset takes the same list from the other
+// end, so the value of a cell pair does not depend on its order.
+struct NearTap {
+    double w;       // weights include the step length: the sum is the optical depth
+    int off, pad;   // off: from the pair's lower end, in the staged box of k_near_blocks
+};
+struct NearList {
+    double fac;     // G / exp(-tau) at this offset
+    int start, count;
+};
+constexpr int kNearLeaf = 8;                       // cells per leaf side (the plan's limit)
+constexpr int kNearRow = 24, kNearPlane = 376;     // pitch of a row and a plane of the staged box (16 x 16 x 16 cells)
+constexpr int kNearThreads = 1024, kNearPlanes = 4;
 
-__global__ __launch_bounds__(kNearLdsThreads) void k_near_blocks(
-    DevTree t, Geo g, const double* __restrict__ st, const double* __restrict__ itab, const int* __restrict__ ua,
-    const int* __restrict__ ub, long u0, uint16_t* __restrict__ blk, int16_t* __restrict__ lo_plane)
+// Offsets d, |d_a| < 2 L, as one index; the list of an offset starts at start[index].
+__host__ __device__ inline int near_list(int L, int d0, int d1, int d2)
 {
-    constexpr int P = kNearLdsSide;  // LDS pitch of a row and (P * P) of a plane
-    __shared__ double sl[P * P * P];
-    const long u = u0 + blockIdx.x;
-    const int per = t.S * t.S;
+    const int R = 2 * L - 1, side = 4 * L - 1;
+    return (d0 + R) + side * ((d1 + R) + side * (d2 + R));
+}
+
+// Cells a ray of offset d can touch: eight at its first sample, at most four more for each
+// cell face it crosses; lists are padded to a multiple of four taps of weight zero.
+__host__ __device__ inline int near_taps_max(int d0, int d1, int d2)
+{
+    return 8 + 4 * (abs(d0) + abs(d1) + abs(d2));
+}
+
+__host__ __device__ inline bool near_lower(int d0, int d1, int d2)
+{
+    return d2 > 0 || (d2 == 0 && (d1 > 0 || (d1 == 0 && d0 > 0)));
+}
+
+// One wave per offset index; list[index].start is given.
+__global__ __launch_bounds__(64) void k_near_taps(Geo g, int L, const double* __restrict__ itab,
+                                                  NearList* __restrict__ list, NearTap* __restrict__ taps)
+{
+    constexpr int B = 2 * kNearLeaf;               // corners -(2 L - 1) .. 0 or 0 .. 2 L - 1 per axis
+    __shared__ double acc[B * B * B];
+    const int D = g.dim, R = 2 * L - 1, side = 4 * L - 1, li = blockIdx.x, lane = threadIdx.x;
+    const int d[3] = {li % side - R, (li / side) % side - R, D > 2 ? li / (side * side) - R : 0};
+    if (D == 2 && li / (side * side) != R) return;
+    if (!near_lower(d[0], d[1], d[2])) return;
+    const int e0 = abs(d[0]) + 1, e1 = abs(d[1]) + 1, e2 = abs(d[2]) + 1, vol = e0 * e1 * e2;
+    const int l0 = d[0] < 0 ? d[0] : 0, l1 = d[1] < 0 ? d[1] : 0, l2 = d[2] < 0 ? d[2] : 0;
+    for (int i = lane; i < vol; i += 64) acc[i] = 0.0;
+    __syncthreads();
+    const int K = d[0] * d[0] + d[1] * d[1] + d[2] * d[2], m = steps_grid(K);
+    const double r = g.h * sqrt((double)K), step = r / double(m);
+    for (int q = 1; q <= m; ++q) {
+        if (lane < 8) {
+            double w = 1.0;
+            int k[3];
+            for (int a = 0; a < 3; ++a) {
+                const int num = (2 * q - 1) * d[a], den = 2 * m;      // position num / den
+                const int f = num >= 0 ? num / den : -((den - 1 - num) / den), rem = num - f * den;
+                const bool up = (lane >> a) & 1;
+                k[a] = f + (up ? 1 : 0);
+                w *= double(up ? rem : den - rem) / double(den);
+            }
+            if (w != 0.0) acc[(k[0] - l0) + e0 * ((k[1] - l1) + e1 * (k[2] - l2))] += w;
+        }
+        __syncthreads();
+    }
+    NearTap* out = taps + list[li].start;
+    int n = 0;
+    for (int i0 = 0; i0 < vol; i0 += 64) {
+        const int i = i0 + lane;
+        const double w = i < vol ? acc[i] : 0.0;
+        const unsigned long long has = __ballot(w != 0.0);
+        if (w != 0.0) {
+            const int x = i % e0 + l0, y = (i / e0) % e1 + l1, z = i / (e0 * e1) + l2;
+            out[n + __popcll(has & ((1ull << lane) - 1))] = NearTap{step * w, x + kNearRow * y + kNearPlane * z, 0};
+        }
+        n += __popcll(has);
+    }
+    const int pad = (4 - (n & 3)) & 3;
+    if (lane < pad) out[n + lane] = NearTap{0.0, 0, 0};
+    if (lane > 0) return;
+    list[li].count = n + pad;
+    const int q0 = abs(d[0]), q1 = abs(d[1]), q2 = abs(d[2]);
+    if (!itab) list[li].fac = 1.0 / (surface_area(D) * (D == 2 ? r : r * r));
+    else if (q0 < g.n0 && q1 < g.n1 && q2 < g.n2)
+        list[li].fac = itab[q0 + (long)g.n0 * (q1 + (long)g.n1 * q2)] / (surface_area(D) * (D == 2 ? g.h : g.h * g.h));
+    else list[li].fac = 0.0;
+}
+
+// 0, 1, -1, 2, -2, ..
+__host__ __device__ inline int near_zigzag(int i) { return (i & 1) ? (i + 1) / 2 : -(i / 2); }
+
+// Stages of a stored pair: one offset in z and up to kNearPlanes of the plane pairs that have it.
+inline int near_stages(int D, int L)
+{
+    int n = 0;
+    for (int i = 0; i < (D > 2 ? 2 * L - 1 : 1); ++i) {
+        const int dz = near_zigzag(i);
+        n += ((D > 2 ? L - abs(dz) : 1) + kNearPlanes - 1) / kNearPlanes;
+    }
+    return n;
+}
+
+// NCH x 64 cell pairs of one offset: sums of the stencil from the staged cells a[j].
+template <int NCH>
+__device__ __forceinline__ void near_sums(const double* sl, const int (&a)[4], const NearTap* __restrict__ taps, int cnt,
+                                          double (&s)[4])
+{
+    const int lane = threadIdx.x & 63;
+    const int4* list = reinterpret_cast<const int4*>(taps);
+    for (int t0 = 0; t0 < cnt; t0 += 64) {
+        const int n = cnt - t0 < 64 ? cnt - t0 : 64;
+        const int4 v = list[t0 + (lane < n ? lane : 0)];
+        for (int i = 0; i < n; i += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const double w = __hiloint2double(__builtin_amdgcn_readlane(v.y, i + u),
+                                                  __builtin_amdgcn_readlane(v.x, i + u));
+                const int off = __builtin_amdgcn_readlane(v.z, i + u);
+#pragma unroll
+                for (int j = 0; j < NCH; ++j) s[j] = fma(w, sl[a[j] + off], s[j]);
+            }
+    }
+}
+
+// One workgroup per (stored pair u, stage) (pairs u0 .. ; blk and lo_plane point at pair
+// u0): element [si][ti] of a block = G(cell ti of leaf ua[u], cell si of leaf ub[u]), zero
+// for a cell with itself (the diagonal's term).  FP32 values as a BF16-rounded high plane
+// and the exact remainder.  sigma_t over the planes between the two ends (cells outside
+// the grid repeat the face) is staged in LDS.  A wave takes an offset at a time, largest
+// share first; its lanes are the cell pairs that have it, so a tap is one weight for the
+// wave and neighbouring reads.  The values go through LDS, where a stage's rows of a
+// block are whole lines.
+// Bound: vector instructions (three per wave and tap, two more per 64 pairs), then LDS
+// reads (48^3: 41.5 -> 16.7 ms, 0.3 ms of stencils more; the march read eight corners per
+// sample with bank conflicts and searched the cell of each).
+__global__ __launch_bounds__(kNearThreads) void k_near_blocks(
+    DevTree t, Geo g, const double* __restrict__ st, const int* __restrict__ ua, const int* __restrict__ ub, long u0,
+    int nstage, const NearList* __restrict__ list,
+    const NearTap* __restrict__ taps, uint16_t* __restrict__ blk, int16_t* __restrict__ lo_plane)
+{
+    __shared__ double sl[2 * kNearLeaf * kNearPlane];
+    __shared__ __align__(16) float val[kNearPlanes * kNearLeaf * kNearLeaf * kNearLeaf * kNearLeaf];
+    __shared__ int next;
+    const long u = u0 + blockIdx.x / nstage;
+    const int L = t.leaf, lane = threadIdx.x & 63;
     const int n[3] = {g.n0, g.n1, g.n2};
-    int bt[3], bs[3], lo[3], ext[3];
+    int bt[3], bs[3];
     unravel3(ua[u], t.nb, bt);
     unravel3(ub[u], t.nb, bs);
-    for (int a = 0; a < 3; ++a) {
-        if (a < t.D) {
-            // lowest cell: the leaves' first, or n - 2 when the clamped search
-            // (k <= n - 2) reaches below a one-cell leaf on the top face
-            int l0 = (bt[a] < bs[a] ? bt[a] : bs[a]) * t.leaf;
-            l0 = (n[a] > 1 && l0 > n[a] - 2) ? n[a] - 2 : l0;
-            int hi = ((bt[a] > bs[a] ? bt[a] : bs[a]) + 1) * t.leaf + 1;
-            hi = hi < n[a] ? hi : n[a];
-            lo[a] = l0;
-            ext[a] = hi - l0;
-        } else {
-            lo[a] = 0;
-            ext[a] = 1;
+    // this stage: planes z0 .. z0 + nc - 1 of the target leaf with those dz above them
+    int dl = 0, z0 = 0, nc = 1;
+    if (t.D > 2) {
+        int sidx = blockIdx.x % nstage;
+        for (int i = 0;; ++i) {
+            dl = near_zigzag(i);
+            const int V = L - abs(dl), ng = (V + kNearPlanes - 1) / kNearPlanes;
+            if (sidx < ng) {
+                z0 = (dl < 0 ? -dl : 0) + kNearPlanes * sidx;
+                nc = V - kNearPlanes * sidx < kNearPlanes ? V - kNearPlanes * sidx : kNearPlanes;
+                break;
+            }
+            sidx -= ng;
         }
     }
-    // staged box: at least two layers per axis (an axis of one cell repeats it,
-    // so its upper corner reads the same value as sigma_at's zero offset)
-    const int sx0 = ext[0] > 1 ? ext[0] : 2, sx1 = ext[1] > 1 ? ext[1] : 2, sx2 = ext[2] > 1 ? ext[2] : 2;
-    for (int e = threadIdx.x; e < sx0 * sx1 * sx2; e += kNearLdsThreads) {
-        const int x0 = e % sx0, x1 = (e / sx0) % sx1, x2 = e / (sx0 * sx1);
-        const int c0 = lo[0] + (x0 < ext[0] ? x0 : ext[0] - 1), c1 = lo[1] + (x1 < ext[1] ? x1 : ext[1] - 1);
-        const int c2 = lo[2] + (x2 < ext[2] ? x2 : ext[2] - 1);
-        sl[x0 + P * (x1 + P * x2)] = st[c0 + (long)g.n0 * (c1 + (long)g.n1 * c2)];
+    const int o0 = L * (bs[0] - bt[0]), o1 = L * (bs[1] - bt[1]), dz = t.D > 2 ? L * (bs[2] - bt[2]) + dl : 0;
+    const int x0 = L * (bt[0] < bs[0] ? bt[0] : bs[0]), y0 = L * (bt[1] < bs[1] ? bt[1] : bs[1]);
+    const int pz = t.D > 2 ? L * bt[2] + z0 + (dz < 0 ? dz : 0) : 0;
+    {
+        const int ex = L + abs(o0), ey = L + abs(o1), np = abs(dz) + nc;
+        for (int e = threadIdx.x; e < ex * ey * np; e += kNearThreads) {
+            const int x = e % ex, y = (e / ex) % ey, z = e / (ex * ey);
+            const int c0 = x0 + x < n[0] ? x0 + x : n[0] - 1, c1 = y0 + y < n[1] ? y0 + y : n[1] - 1;
+            const int c2 = pz + z < n[2] ? pz + z : n[2] - 1;
+            sl[x + kNearRow * y + kNearPlane * z] = st[c0 + (long)n[0] * (c1 + (long)n[1] * (t.D > 2 ? c2 : 0))];
+        }
+    }
+    if (threadIdx.x == 0) next = 0;
+    __syncthreads();
+    const int S2 = L * L, side = 2 * L - 1;
+    // both leaves whole: every element of their blocks is a cell pair of the grid
+    bool whole = true;
+    for (int a = 0; a < t.D; ++a) whole = whole && L * ((bt[a] > bs[a] ? bt[a] : bs[a]) + 1) <= n[a];
+    for (;;) {
+        int i = 0;
+        if (lane == 0) i = atomicAdd(&next, 1);
+        i = __builtin_amdgcn_readfirstlane(i);
+        if (i >= side * side) break;
+        const int dx = near_zigzag(i % side), dy = near_zigzag(i / side);
+        const int Vx = L - abs(dx), Vy = L - abs(dy), V = Vx * Vy * nc, nch = (V + 63) / 64;
+        const int d0 = o0 + dx, d1 = o1 + dy;
+        const int K = d0 * d0 + d1 * d1 + dz * dz;
+        const bool lower = near_lower(d0, d1, dz);
+        const int tx0 = dx < 0 ? -dx : 0, ty0 = dy < 0 ? -dy : 0;
+        NearList nl{0.0, 0, 0};
+        if (K > 0) nl = list[lower ? near_list(L, d0, d1, dz) : near_list(L, -d0, -d1, -dz)];
+        // e < 256 over Vx, then Vy, by multiplication (exact for these sizes)
+        const unsigned mx = 65536u / (unsigned)Vx + 1, my = 65536u / (unsigned)Vy + 1;
+        const int a0 = L * bt[0] + tx0 - x0 + (lower ? 0 : d0), a1 = L * bt[1] + ty0 - y0 + (lower ? 0 : d1);
+        const int a2 = (dz < 0 ? -dz : 0) + (lower ? 0 : dz);
+        const int cell0 = a0 + kNearRow * a1 + kNearPlane * a2;
+        const int slot0 = (tx0 + dx + L * (ty0 + dy)) * S2 + tx0 + L * ty0;
+        int a[4] = {0, 0, 0, 0}, slot[4] = {-1, -1, -1, -1};
+        bool in[4] = {true, true, true, true};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= nch) break;
+            const int e = 64 * j + lane, ec = e < V ? e : V - 1;
+            const int q = (int)((unsigned)__mul24(ec, mx) >> 16), z = (int)((unsigned)__mul24(q, my) >> 16);
+            const int x = ec - __mul24(q, Vx), y = q - __mul24(z, Vy);
+            a[j] = cell0 + x + __mul24(kNearRow, y) + __mul24(kNearPlane, z);
+            if (e < V) slot[j] = slot0 + __mul24(x, S2 + 1) + __mul24(y, L * (S2 + 1)) + __mul24(z, S2 * S2);
+            if (!whole) {
+                const int t0 = L * bt[0] + tx0 + x, t1 = L * bt[1] + ty0 + y, t2 = t.D > 2 ? L * bt[2] + z0 + z : 0;
+                in[j] = t0 < n[0] && t1 < n[1] && t2 < n[2] && t0 + d0 < n[0] && t1 + d1 < n[1] && t2 + dz < n[2];
+            }
+        }
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        const NearTap* tl = taps + nl.start;
+        if (nch == 1) near_sums<1>(sl, a, tl, nl.count, s);
+        else if (nch == 2) near_sums<2>(sl, a, tl, nl.count, s);
+        else if (nch == 3) near_sums<3>(sl, a, tl, nl.count, s);
+        else near_sums<4>(sl, a, tl, nl.count, s);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j < nch && slot[j] >= 0) val[slot[j]] = in[j] ? (float)(exp(-s[j]) * nl.fac) : 0.0f;
     }
     __syncthreads();
-    const double inv_h = 1.0 / g.h;
-    const bool d3 = t.D > 2;
-    // An axis of one cell (or the third axis in 2D) takes k = 0 and t = 0: its
-    // terms add exact zeros, so a 2D value is sigma_at's c0.
-    const double hiA[3] = {double(n[0] - 1), double(n[1] - 1), double(n[2] - 1)};
-    const double kmA[3] = {double(n[0] > 1 ? n[0] - 2 : 0), double(n[1] > 1 ? n[1] - 2 : 0),
-                           double(n[2] > 1 ? n[2] - 2 : 0)};
-    const double off = fma(double(P * P), double(lo[2]), fma(double(P), double(lo[1]), double(lo[0])));
-    const int L = t.leaf, L1 = t.D > 1 ? t.leaf : 1;
-    uint16_t* bo = blk + (u - u0) * (long)per;
-    int16_t* lp = lo_plane + (u - u0) * (long)per;
-    for (int i = threadIdx.x; i < per; i += kNearLdsThreads) {
-        const int si = i / t.S, ti = i - (i / t.S) * t.S;
-        double v = 0.0;
-        // cells of slot ti of the target leaf and slot si of the source leaf
-        const int ct[3] = {bt[0] * L + ti % L, t.D > 1 ? bt[1] * L + (ti / L) % L1 : 0,
-                           t.D > 2 ? bt[2] * L + ti / (L * L1) : 0};
-        const int cs[3] = {bs[0] * L + si % L, t.D > 1 ? bs[1] * L + (si / L) % L1 : 0,
-                           t.D > 2 ? bs[2] * L + si / (L * L1) : 0};
-        const bool in = ct[0] < n[0] && ct[1] < n[1] && ct[2] < n[2] && cs[0] < n[0] && cs[1] < n[1] &&
-                        cs[2] < n[2];
-        const long jt = ct[0] + (long)n[0] * (ct[1] + (long)n[1] * ct[2]);
-        const long js = cs[0] + (long)n[0] * (cs[1] + (long)n[1] * cs[2]);
-        if (in && jt != js) {
-            int K = 0;
-            for (int a = 0; a < 3; ++a) K += (ct[a] - cs[a]) * (ct[a] - cs[a]);
-            const double r = g.h * sqrt((double)K);
-            const int* pa = (jt < js) ? ct : cs;
-            const int* pb = (jt < js) ? cs : ct;
-            const double a0 = g.h * (pa[0] + 0.5), a1 = g.h * (pa[1] + 0.5), a2 = d3 ? g.h * (pa[2] + 0.5) : 0.0;
-            const double e0 = g.h * (pb[0] + 0.5) - a0, e1 = g.h * (pb[1] + 0.5) - a1;
-            const double e2 = (d3 ? g.h * (pb[2] + 0.5) : 0.0) - a2;
-            const int m = steps_grid(K);
-            const double inv_m = 1.0 / double(m);
-            double s = 0.0;
-            for (int q = 1; q <= m; ++q) {
-                const double f = (double(q) - 0.5) * inv_m;
-                const double u0 = fmin(fmax((a0 + f * e0) * inv_h - 0.5, 0.0), hiA[0]);
-                const double u1 = fmin(fmax((a1 + f * e1) * inv_h - 0.5, 0.0), hiA[1]);
-                const double u2 = fmin(fmax((a2 + f * e2) * inv_h - 0.5, 0.0), hiA[2]);
-                const double k0 = fmin(floor(u0), kmA[0]), k1 = fmin(floor(u1), kmA[1]);
-                const double k2 = fmin(floor(u2), kmA[2]);
-                const double t0 = u0 - k0, t1 = u1 - k1, t2 = u2 - k2;
-                const double* c = sl + (int)(fma(double(P * P), k2, fma(double(P), k1, k0)) - off);
-                double c00 = c[0] + t0 * (c[1] - c[0]);
-                double c10 = c[P] + t0 * (c[P + 1] - c[P]);
-                double c0 = c00 + t1 * (c10 - c00);
-                double c01 = c[P * P] + t0 * (c[P * P + 1] - c[P * P]);
-                double c11 = c[P * P + P] + t0 * (c[P * P + P + 1] - c[P * P + P]);
-                double c1 = c01 + t1 * (c11 - c01);
-                s += c0 + t2 * (c1 - c0);
-            }
-            const double tau = r * inv_m * s;
-            if (itab) {
-                const int o0 = abs(ct[0] - cs[0]), o1 = abs(ct[1] - cs[1]), o2 = abs(ct[2] - cs[2]);
-                const double hp = (t.D == 2) ? g.h : g.h * g.h;
-                v = exp(-tau) * itab[o0 + (long)g.n0 * (o1 + (long)g.n1 * o2)] / (surface_area(t.D) * hp);
-            } else {
-                const double rp = (t.D == 2) ? r : r * r;
-                v = exp(-tau) / (surface_area(t.D) * rp);
-            }
+    const long base = (u - u0) * (long)t.S * t.S;
+    const int plane = S2 * S2;
+    auto split = [](float v, uint16_t& h, int16_t& l) {
+        const unsigned X = __float_as_uint(v), hi = (X + 0x8000u) >> 16;
+        h = (uint16_t)hi;
+        l = (int16_t)(int)(X - (hi << 16));
+    };
+    // four elements per thread where rows are whole groups of four (even leaves)
+    const int W = (S2 & 3) ? 1 : 4;
+    for (int e = W * threadIdx.x; e < nc * plane; e += W * kNearThreads) {
+        const int z = e / plane, r = e - z * plane, si = r / S2, ti = r - si * S2;
+        const long i = base + (long)(S2 * (z0 + z + dl) + si) * t.S + S2 * (z0 + z) + ti;
+        if (W == 4) {
+            const float4 v = *reinterpret_cast<const float4*>(val + e);
+            ushort4 h;
+            short4 l;
+            split(v.x, h.x, l.x);
+            split(v.y, h.y, l.y);
+            split(v.z, h.z, l.z);
+            split(v.w, h.w, l.w);
+            *reinterpret_cast<ushort4*>(blk + i) = h;
+            *reinterpret_cast<short4*>(lo_plane + i) = l;
+        } else {
+            split(val[e], blk[i], lo_plane[i]);
         }
-        const unsigned X = __float_as_uint((float)v);
-        const unsigned hi = (X + 0x8000u) >> 16;
-        bo[i] = (uint16_t)hi;
-        lp[i] = (int16_t)(int)(X - (hi << 16));
     }
 }
 
@@ -1761,6 +1901,42 @@ ert_status FmmImpl<T>::setup_far_hom(ert_plan_impl* p, int l, double svd_tol)
 // for target t and source s (the transpose serves target s).
 // The corner-octet table of the plan's sigma_t, held while the caches are built
 // (8 doubles per cell); the stream is drained before it is released.
+// The np stored near-field blocks of the cache (k_near_blocks) from freshly formed stencils.
+ert_status near_blocks(ert_plan_impl* p, const DevTree& dt, HetCache* c, long np)
+{
+    hipStream_t s = p->stream;
+    const int L = dt.leaf, side = 4 * L - 1, R = 2 * L - 1;
+    std::vector<NearList> list((size_t)side * side * side, NearList{0.0, 0, 0});
+    int total = 0;
+    for (int d2 = dt.D > 2 ? -R : 0; d2 <= (dt.D > 2 ? R : 0); ++d2)
+        for (int d1 = -R; d1 <= R; ++d1)
+            for (int d0 = -R; d0 <= R; ++d0)
+                if (near_lower(d0, d1, d2)) {
+                    list[near_list(L, d0, d1, d2)].start = total;
+                    total += near_taps_max(d0, d1, d2);
+                }
+    DevPtrs tmp;
+    NearTap* taps = nullptr;
+    static_assert(sizeof(NearList) == sizeof(NearTap), "one buffer: stencils, then their lists");
+    ERT_TRY(tmp.alloc(&taps, (size_t)total + list.size()));
+    NearList* d_list = reinterpret_cast<NearList*>(taps + total);
+    ERT_HIP(hipMemcpyAsync(d_list, list.data(), list.size() * sizeof(NearList), hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(k_near_taps, dim3((unsigned)list.size()), dim3(64), 0, s, p->geo, L, p->d_itab, d_list, taps);
+    ERT_HIP(hipGetLastError());
+    const int nstage = near_stages(dt.D, L);
+    const long per = (long)dt.S * dt.S;
+    const long chunk = std::max<long>(1, std::min((1L << 28) / per, (1L << 21) / nstage));
+    for (long u0 = 0; u0 < np; u0 += chunk) {
+        const long cnt = std::min(chunk, np - u0);
+        hipLaunchKernelGGL(k_near_blocks, dim3((unsigned)(cnt * nstage)), dim3(kNearThreads), 0, s, dt, p->geo, p->d_st,
+                           c->near_ua, c->near_ub, u0, nstage, d_list, taps, c->near_hi + (size_t)u0 * per, c->near_lo + (size_t)u0 * per);
+        ERT_HIP(hipGetLastError());
+    }
+    // the stencils go with the launches that read them
+    ERT_HIP(hipStreamSynchronize(s));
+    return ERT_OK;
+}
+
 struct CornerTable {
     double* st8 = nullptr;
     hipStream_t s = nullptr;
@@ -2072,18 +2248,11 @@ ert_status FmmImpl<T>::setup_het(ert_plan_impl* p)
     CornerTable t8;
     if (st == ERT_OK) st = t8.build(p);
     if (st != ERT_OK) return fail(st);
-    if (tr.leaf > kNearLdsLeaf) {
+    if (tr.leaf > kNearLeaf) {
         record_error("FMM: leaf larger than the near-field block kernel supports");
         return fail(ERT_EINVAL);
     }
-    const long chunk = std::max<long>(1, (1L << 28) / per);
-    for (long u0 = 0; u0 < np; u0 += chunk) {
-        const long cnt = std::min(chunk, np - u0);
-        hipLaunchKernelGGL(k_near_blocks, dim3((unsigned)cnt), dim3(kNearLdsThreads), 0, s, dt, p->geo, p->d_st,
-                           p->d_itab, c->near_ua, c->near_ub, u0, c->near_hi + (size_t)u0 * per,
-                           c->near_lo + (size_t)u0 * per);
-        if (hipGetLastError() != hipSuccess) return fail(ERT_EDEVICE);
-    }
+    st = near_blocks(p, dt, c, np);
     for (int l = 2; l <= tr.L && st == ERT_OK; ++l) st = het_far_level(p, tr, cheb, t8.st8, c, l);
     if (st == ERT_OK && hipStreamSynchronize(s) != hipSuccess) st = ERT_EDEVICE;
     if (st != ERT_OK) return fail(st);

@@ -2,6 +2,8 @@
 import numpy as np
 import pytest
 
+from tests.gpu_util import gpu_apply
+
 pytestmark = pytest.mark.gpu
 
 
@@ -21,3 +23,30 @@ def test_diagonal_of_rough_medium(ev, oracle_mod, n, h):
     P = oracle_mod.Problem(len(n), n, h, 1, st, 0.9 * st)
     with ev.Plan(len(n), n, h, st, 0.9 * st, kernel=1) as plan:
         np.testing.assert_allclose(plan.diag(), P.diag(), rtol=1e-13, atol=0)
+
+
+@pytest.mark.parametrize("n,h,leaf,scheme", [
+    ((16, 16, 16), 1.0 / 16, 0, 0),      # all 14 pairs of full leaves
+    ((13, 16, 9), 0.07, 0, 0),           # ragged, spacing whose reciprocal rounds
+    ((16, 3, 8), 1.0 / 19, 0, 0),       # the same from the lowest cell of the second leaf
+    ((1, 9, 16), 0.3, 0, 0),             # one cell thick
+    ((10, 7, 9), 0.11, 5, 0),            # odd leaves
+    ((6, 5, 6), 0.2, 3, 1),              # cell integrals instead of point values
+    ((4, 3, 4), 0.2, 2, 0),
+    ((15, 16), 0.09, 0, 0),
+    ((6, 5), 0.3, 3, 1),
+])
+def test_near_blocks(ev, oracle_mod, n, h, leaf, scheme):
+    """Products of two leaves per axis are all near field: G w with w > 0 and entries > 0 is
+    off by the FP32 rounding of the stored values (2^-24) at most, per element."""
+    N = int(np.prod(n))
+    rng = np.random.default_rng(N)
+    st = 10.0 ** rng.uniform(-1.0, 1.5, size=N)
+    P = oracle_mod.Problem(len(n), n, h, 1, st, 0.9 * st, scheme=scheme)
+    x = rng.uniform(0.5, 1.0, size=N)
+    want = P.apply(x, op=ev.OP_G)
+    with ev.Plan(len(n), n, h, st, 0.9 * st, kernel=1, method="fmm", cheb_n=8, leaf=leaf, scheme=scheme) as plan:
+        got = gpu_apply(plan, x, ev.OP_G)
+        again = gpu_apply(plan, x, ev.OP_G)
+    assert np.array_equal(got, again)
+    np.testing.assert_allclose(got, want, rtol=7e-8, atol=0)
