@@ -1017,81 +1017,99 @@ __global__ void k_ops_het(Geo g, const double* __restrict__ st8, int D, int nc, 
 }
 
 
-// The same matrices (3D, every grid side > 1) with sigma_t read from LDS.  A
-// workgroup takes kOpsLdsRays x kOpsLdsThreads entries of one pair and marches
-// them window by window in the ray parameter: window w holds, for a ray of m
-// steps, the samples q in (w m / nwin, (w + 1) m / nwin].  Their points lie in
-// the box swept by (1 - f) A + f B for f in [w / nwin - 1/(2m), (w + 1) / nwin]
-// (A, B the two boxes; the shift below w / nwin is at most half a step, a
-// quarter cell), so sigma_t over that box plus one cell of margin on each side
-// is staged before the window.  Each ray keeps its running sum across windows:
-// the samples are added in the order q = 1 .. m and every value matches
-// k_ops_het bit for bit.  A window whose box exceeds the LDS capacity reads
-// the corner-octet table instead.
-constexpr int kOpsLdsThreads = 512;
-constexpr int kOpsLdsRays = 2;
-constexpr int kOpsLdsSide = 18;   // cells per axis of a staged box (LDS pitch; 18^3 doubles = 46.7 KB)
+// The same matrices (3D) with sigma_t read from LDS.  A workgroup takes kOpsRays x
+// kOpsThreads entries of one pair and marches them window by window in the ray
+// parameter: window i holds, for a ray of m steps, the samples q in (i m / nwin,
+// (i + 1) m / nwin].  Their points lie in the box swept by (1 - f) A + f B for f in
+// [i / nwin - 1/(2m), (i + 1) / nwin] (A, B the two boxes; the shift below i / nwin is
+// at most half a step, a quarter cell), so sigma_t over that box plus one cell of margin
+// on each side is staged before the window, cells outside the grid with the value of the
+// face: the clamped interpolation without a clamp.  The samples are added in the order
+// q = 1 .. m; a sample's point is one fused multiply-add per axis in cells of the box.
+// Bound: LDS reads (eight corners per sample) and the thirty vector instructions of a
+// sample.  Eight rays per thread share a staged box of up to 21 cells a side (two rays
+// and 18 cells spent more on staging than on samples).  A wave's rays differ in the x
+// nodes first: their cells at a time lie in one or two rows of the box, shared or on
+// different banks (simulated with these pitches 1.08 cycles per 16 lanes; 1.9 with the
+// target's nodes in order and pitches of 18).  48^3, order 6: 59 -> 37 ms.
+constexpr int kOpsThreads = 512;
+constexpr int kOpsRays = 8;
+constexpr int kOpsSide = 21;                       // cells per axis of a staged box
+constexpr int kOpsRow = 21, kOpsPlane = 460;       // LDS pitch of a row and a plane
+constexpr int kOpsMaxSteps = 255;
+
+// Windows of a pair of boxes of wc cells a side, omax boxes apart: the fewest whose staged
+// boxes fit; 0 when none up to 32 do.
+__host__ __device__ inline int ops_windows(int wc, int omax)
+{
+    for (int nw = 1; nw <= 32; ++nw)
+        if (wc + (omax * wc + nw - 1) / nw + 5 <= kOpsSide) return nw;
+    return 0;
+}
+
+// one copy of the integral for the rays of a thread
+__device__ __noinline__ double far_cell_int(double d0, double d1, double d2) { return cell_int(3, d0, d1, d2, 64.0); }
 
 template <typename T, bool MII>
-__global__ __launch_bounds__(kOpsLdsThreads) void k_ops_het_lds(
-    Geo g, const double* __restrict__ st, const double* __restrict__ st8, int nc, int K, int Kp, double w, int nl0,
-    int nl1, int nl2, const double* __restrict__ cheb, const int* __restrict__ pair_t, const int* __restrict__ pair_s,
-    long p0, int ngroup, int nwin, T* __restrict__ opsT)
+__global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
+    Geo g, const double* __restrict__ st, int nc, int K, int Kp, double w, int wc, int nl0, int nl1, int nl2,
+    const double* __restrict__ cheb, const int* __restrict__ pair_t, const int* __restrict__ pair_s, long p0, int ngroup,
+    T* __restrict__ opsT)
 {
-    constexpr int R = kOpsLdsRays;
-    constexpr int P = kOpsLdsSide;
-    __shared__ double sl[P * P * P];
+    constexpr int R = kOpsRays;
+    __shared__ double sl[(kOpsSide - 1) * (kOpsPlane + kOpsRow) + kOpsSide];
+    __shared__ double inv[kOpsMaxSteps + 1];
+    __shared__ double X[3][8], Y[3][8];            // node coordinates of the two boxes
     const long pl = blockIdx.x / ngroup;
     const long p = p0 + pl;
-    const int gi = (int)(blockIdx.x - pl * ngroup);
-    const int per = Kp * Kp;
+    const int gi = (int)(blockIdx.x - pl * ngroup), tid = threadIdx.x;
     const int nl[3] = {nl0, nl1, nl2};
     int tb[3], sb[3];
     unravel3(pair_t[p], nl, tb);
     unravel3(pair_s[p], nl, sb);
     const double inv_h = 1.0 / g.h;
     const int n[3] = {g.n0, g.n1, g.n2};
-    const double hi0 = double(n[0] - 1), hi1 = double(n[1] - 1), hi2 = double(n[2] - 1);
-    const double km0 = double(n[0] - 2), km1 = double(n[1] - 2), km2 = double(n[2] - 2);
+    int omax = 0;
+    for (int a = 0; a < 3; ++a) omax = abs(sb[a] - tb[a]) > omax ? abs(sb[a] - tb[a]) : omax;
+    const int nwin = ops_windows(wc, omax);
+    for (int i = tid; i <= kOpsMaxSteps; i += kOpsThreads) inv[i] = 1.0 / double(i);
+    if (tid < 3 * nc) {
+        const int a = tid / nc, i = tid - a * nc;
+        X[a][i] = node_coord(w, tb[a], cheb[i]);
+        Y[a][i] = node_coord(w, sb[a], cheb[i]);
+    }
+    __syncthreads();
 
-    double ra[R][3], re[R][3], rinv[R], rs[R], rlen[R], r2s[R];
-    int rm[R], ri[R];
+    // a ray: its sum, six node indices of four bits and its step count
+    double rs[R];
+    unsigned ray[R];
+    auto dist2 = [&](unsigned nd) {
+        double r2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            const double d = Y[a][nd >> (4 * a + 12) & 15] - X[a][nd >> (4 * a) & 15];
+            r2 = fma(d, d, r2);
+        }
+        return r2;
+    };
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int e = gi * (R * kOpsLdsThreads) + j * kOpsLdsThreads + (int)threadIdx.x;
-        ri[j] = e;
-        rm[j] = 0;
+        const int e = gi * (R * kOpsThreads) + j * kOpsThreads + tid;
         rs[j] = 0.0;
-        rinv[j] = 1.0;
-        rlen[j] = 0.0;
-        r2s[j] = 0.0;
-        for (int a = 0; a < 3; ++a) ra[j][a] = re[j][a] = 0.0;
-        const int c = e / Kp, r = e - (e / Kp) * Kp;
-        if (e < per && r < K && c < K) {
-            int mr[3], mc[3];
-            node_multi(r, nc, 3, mr);
-            node_multi(c, nc, 3, mc);
-            double X[3], Y[3], r2 = 0.0;
-            for (int a = 0; a < 3; ++a) {
-                X[a] = node_coord(w, tb[a], cheb[mr[a]]);
-                Y[a] = node_coord(w, sb[a], cheb[mc[a]]);
-                r2 = fma(Y[a] - X[a], Y[a] - X[a], r2);
+        ray[j] = 0;
+        if (e < K * K) {
+            // digits of e: the two x nodes, then y and z of the target, y and z of the source
+            unsigned nd = 0, rest = e;
+            constexpr int shift[6] = {0, 12, 4, 8, 16, 20};
+            for (int i = 0; i < 6; ++i) {
+                nd |= (rest % nc) << shift[i];
+                rest /= nc;
             }
-            const double rr = sqrt(r2);
-            const double q = ceil(rr / (0.5 * g.h));
-            const int m = q < 1.0 ? 1 : (int)q;
-            for (int a = 0; a < 3; ++a) {
-                ra[j][a] = X[a];
-                re[j][a] = Y[a] - X[a];
-            }
-            rm[j] = m;
-            rinv[j] = 1.0 / double(m);
-            rlen[j] = rr;
-            r2s[j] = r2;
+            const double q = ceil(sqrt(dist2(nd)) / (0.5 * g.h));
+            ray[j] = nd | (unsigned)(q < 1.0 ? 1 : (int)q) << 24;
         }
     }
 
-    const double2* q8 = reinterpret_cast<const double2*>(st8);
+    const float inv_nwin = 1.0f / (float)nwin;
     for (int wi = 0; wi < nwin; ++wi) {
         const double F0 = double(wi) / nwin, F1 = double(wi + 1) / nwin;
         int kmin[3], ext[3];
@@ -1100,109 +1118,80 @@ __global__ __launch_bounds__(kOpsLdsThreads) void k_ops_het_lds(
             const double l0 = Al + F0 * d, l1 = Al + F1 * d;
             const double lo_pos = l0 < l1 ? l0 : l1;
             const double hi_pos = (l0 > l1 ? l0 : l1) + w;
-            int k0 = (int)floor(lo_pos * inv_h - 0.5) - 1;
-            int k1 = (int)floor(hi_pos * inv_h - 0.5) + 2;
-            k0 = k0 < 0 ? 0 : (k0 > n[a] - 2 ? n[a] - 2 : k0);
-            k1 = k1 > n[a] - 1 ? n[a] - 1 : k1;
-            k1 = k1 < k0 + 1 ? k0 + 1 : k1;
-            kmin[a] = k0;
-            ext[a] = k1 - k0 + 1;
+            kmin[a] = (int)floor(lo_pos * inv_h - 0.5) - 1;
+            const int e = (int)floor(hi_pos * inv_h - 0.5) + 3 - kmin[a];
+            ext[a] = e < kOpsSide ? e : kOpsSide;
         }
-        const int nst = ext[0] * ext[1] * ext[2];
-        const bool lds = ext[0] <= P && ext[1] <= P && ext[2] <= P;
         __syncthreads();  // the previous window's reads are done
-        if (lds) {
-            for (int e = threadIdx.x; e < nst; e += kOpsLdsThreads) {
-                const int x0 = e % ext[0], x1 = (e / ext[0]) % ext[1], x2 = e / (ext[0] * ext[1]);
-                sl[x0 + P * (x1 + P * x2)] =
-                    st[(kmin[0] + x0) + (long)n[0] * ((kmin[1] + x1) + (long)n[1] * (kmin[2] + x2))];
-            }
+        {
+            // half a wave per row
+            const int x = tid & 31, cx = kmin[0] + x;
+            const long c0 = cx < 0 ? 0 : (cx > n[0] - 1 ? n[0] - 1 : cx);
+            const float inv_ext = 1.0f / (float)ext[1];
+            if (x < ext[0])
+#pragma unroll 4
+                for (int row = tid >> 5; row < ext[1] * ext[2]; row += kOpsThreads / 32) {
+                    const int z = (int)(((float)row + 0.5f) * inv_ext), y = row - z * ext[1];
+                    const int cy = kmin[1] + y, cz = kmin[2] + z;
+                    const long c1 = cy < 0 ? 0 : (cy > n[1] - 1 ? n[1] - 1 : cy);
+                    const long c2 = cz < 0 ? 0 : (cz > n[2] - 1 ? n[2] - 1 : cz);
+                    sl[x + kOpsRow * y + kOpsPlane * z] = st[c0 + n[0] * (c1 + n[1] * c2)];
+                }
         }
         __syncthreads();
-        const double off = fma(double(P * P), double(kmin[2]), fma(double(P), double(kmin[1]), double(kmin[0])));
+        const double b0 = -0.5 - kmin[0], b1 = -0.5 - kmin[1], b2 = -0.5 - kmin[2];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int m = rm[j];
-            const int qa = (wi * m) / nwin + 1, qb = ((wi + 1) * m) / nwin;
-            double s = rs[j];
-            // one sample: the cell search of sigma_at and its interpolation over the
-            // corners c[0], c[dx], c[dy], c[dy + dx], c[dz], ... (LDS box or octet table)
-            auto sample = [&](int q, auto corners) {
-                const double f = (double(q) - 0.5) * rinv[j];
-                const double u0 = fmin(fmax((ra[j][0] + f * re[j][0]) * inv_h - 0.5, 0.0), hi0);
-                const double u1 = fmin(fmax((ra[j][1] + f * re[j][1]) * inv_h - 0.5, 0.0), hi1);
-                const double u2 = fmin(fmax((ra[j][2] + f * re[j][2]) * inv_h - 0.5, 0.0), hi2);
-                const double k0 = fmin(floor(u0), km0), k1 = fmin(floor(u1), km1), k2 = fmin(floor(u2), km2);
+            unsigned nd = ray[j];
+            asm volatile("" : "+v"(nd));          // the node addresses of all rays don't fit in registers
+            const int m = (int)(nd >> 24);
+            // i m / nwin of both ends, exact: the half moves it off the integers
+            const int qa = (int)(((float)(wi * m) + 0.5f) * inv_nwin), qb = (int)(((float)((wi + 1) * m) + 0.5f) * inv_nwin);
+            const double x0 = X[0][nd & 15], x1 = X[1][nd >> 4 & 15], x2 = X[2][nd >> 8 & 15];
+            const double step = inv[m] * inv_h;
+            const double e0 = (Y[0][nd >> 12 & 15] - x0) * step, e1 = (Y[1][nd >> 16 & 15] - x1) * step;
+            const double e2 = (Y[2][nd >> 20 & 15] - x2) * step;
+            const double a0 = fma(x0, inv_h, b0), a1 = fma(x1, inv_h, b1), a2 = fma(x2, inv_h, b2);
+            double s = rs[j], q = qa + 0.5;
+            for (int i = qa; i < qb; ++i, q += 1.0) {
+                const double u0 = fma(q, e0, a0), u1 = fma(q, e1, a1), u2 = fma(q, e2, a2);
+                const double k0 = floor(u0), k1 = floor(u1), k2 = floor(u2);
                 const double t0 = u0 - k0, t1 = u1 - k1, t2 = u2 - k2;
-                double v[8];
-                corners(k0, k1, k2, v);
-                double c00 = v[0] + t0 * (v[1] - v[0]);
-                double c10 = v[2] + t0 * (v[3] - v[2]);
-                double c0 = c00 + t1 * (c10 - c00);
-                double c01 = v[4] + t0 * (v[5] - v[4]);
-                double c11 = v[6] + t0 * (v[7] - v[6]);
-                double c1 = c01 + t1 * (c11 - c01);
-                s += c0 + t2 * (c1 - c0);
-            };
-            if (lds) {
-                auto from_lds = [&](double k0, double k1, double k2, double* v) {
-                    const double* c = sl + (int)(fma(double(P * P), k2, fma(double(P), k1, k0)) - off);
-                    v[0] = c[0];
-                    v[1] = c[1];
-                    v[2] = c[P];
-                    v[3] = c[P + 1];
-                    v[4] = c[P * P];
-                    v[5] = c[P * P + 1];
-                    v[6] = c[P * P + P];
-                    v[7] = c[P * P + P + 1];
-                };
-                for (int q = qa; q <= qb; ++q) sample(q, from_lds);
-            } else {
-                auto from_table = [&](double k0, double k1, double k2, double* v) {
-                    const unsigned cc = (unsigned)fma(double(n[0]), fma(double(n[1]), k2, k1), k0);
-                    const double2* pq = q8 + 4 * (size_t)cc;
-                    for (int x = 0; x < 4; ++x) {
-                        const double2 d = pq[x];
-                        v[2 * x] = d.x;
-                        v[2 * x + 1] = d.y;
-                    }
-                };
-                for (int q = qa; q <= qb; ++q) sample(q, from_table);
+                const double* c = sl + (int)fma(double(kOpsPlane), k2, fma(double(kOpsRow), k1, k0));
+                const double c00 = fma(t0, c[1] - c[0], c[0]);
+                const double c10 = fma(t0, c[kOpsRow + 1] - c[kOpsRow], c[kOpsRow]);
+                const double c01 = fma(t0, c[kOpsPlane + 1] - c[kOpsPlane], c[kOpsPlane]);
+                const double c11 = fma(t0, c[kOpsPlane + kOpsRow + 1] - c[kOpsPlane + kOpsRow], c[kOpsPlane + kOpsRow]);
+                const double c0 = fma(t1, c10 - c00, c00), c1 = fma(t1, c11 - c01, c01);
+                s += fma(t2, c1 - c0, c0);
             }
             rs[j] = s;
         }
     }
 
-    T* out = opsT + pl * (long)per;
+    T* out = opsT + pl * (long)Kp * Kp;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int e = ri[j];
-        if (e >= per) continue;
-        double v = 0.0;
-        if (rm[j] > 0) {
-            const double tau = rlen[j] * rinv[j] * rs[j];
-            if constexpr (MII) {
-                const double hp = g.h * g.h;
-                v = exp(-tau) * cell_int(3, re[j][0] / g.h, re[j][1] / g.h, re[j][2] / g.h, 64.0) /
-                    (surface_area(3) * hp);
-            } else {
-                v = exp(-tau) / (surface_area(3) * r2s[j]);
-            }
+        const int e = gi * (R * kOpsThreads) + j * kOpsThreads + tid;
+        if (e >= K * K) continue;
+        const unsigned nd = ray[j];
+        const double r2 = dist2(nd), tau = sqrt(r2) * inv[nd >> 24] * rs[j];
+        double v;
+        if constexpr (MII) {
+            double d[3];
+            for (int a = 0; a < 3; ++a) d[a] = (Y[a][nd >> (4 * a + 12) & 15] - X[a][nd >> (4 * a) & 15]) / g.h;
+            v = exp(-tau) * far_cell_int(d[0], d[1], d[2]) / (surface_area(3) * g.h * g.h);
+        } else {
+            v = exp(-tau) / (surface_area(3) * r2);
         }
-        out[e] = T(v);
+        const int r = (nd & 15) + nc * ((nd >> 4 & 15) + nc * (nd >> 8 & 15));
+        const int c = (nd >> 12 & 15) + nc * ((nd >> 16 & 15) + nc * (nd >> 20 & 15));
+        out[c * Kp + r] = T(v);
     }
-}
-
-// Windows per pair for k_ops_het_lds at box width w (in cells): the fewest whose
-// boxes fit kOpsLdsSide cells per axis for offsets up to 3 boxes; 0 when none up
-// to 32 do.
-inline int ops_lds_windows(int wc)
-{
-    for (int nw = 1; nw <= 32; ++nw) {
-        const long side = wc + (3L * wc + nw - 1) / nw + 5;
-        if (side <= kOpsLdsSide) return nw;
-    }
-    return 0;
+    // the padding of the matrix
+    if (gi == 0 && Kp > K)
+        for (int i = tid; i < Kp * Kp; i += kOpsThreads)
+            if (i % Kp >= K || i / Kp >= K) out[i] = T(0);
 }
 
 // Near-field coupling of two cells of a homogeneous medium at cell offset dv
@@ -1977,16 +1966,18 @@ ert_status het_fill(ert_plan_impl* p, hipStream_t s, const FmmTree& tr, const do
     const long pchunk = std::max<long>(1, (1L << 27) / KpKp);
     const Geo& g = p->geo;
     const int nl[3] = {tr.nl[l][0], tr.nl[l][1], tr.nl[l][2]};
-    const int nwin = (tr.D == 3 && g.n0 > 1 && g.n1 > 1 && g.n2 > 1) ? ops_lds_windows(tr.leaf << (tr.L - l)) : 0;
-    const long ngroup = (KpKp + kOpsLdsRays * kOpsLdsThreads - 1) / (kOpsLdsRays * kOpsLdsThreads);
+    // wide boxes (16 cells a side and more) do not fit in LDS with the cells between them
+    const int wc = tr.leaf << (tr.L - l);
+    const bool lds = tr.D == 3 && ops_windows(wc, 3) > 0;
+    const long ngroup = ((long)tr.K * tr.K + kOpsRays * kOpsThreads - 1) / (kOpsRays * kOpsThreads);
     for (long q0 = p0; q0 < p0 + cnt; q0 += pchunk) {
         const long c = std::min(pchunk, p0 + cnt - q0);
         float* out = dst + (size_t)(q0 - p0) * KpKp;
-        if (nwin > 0) {
+        if (lds) {
             auto kern = p->o.scheme ? k_ops_het_lds<float, true> : k_ops_het_lds<float, false>;
-            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(kOpsLdsThreads), 0, s, g, p->d_st, st8, tr.nc,
-                               tr.K, tr.Kp, tr.width[l], nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0,
-                               (int)ngroup, nwin, out);
+            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(kOpsThreads), 0, s, g, p->d_st, tr.nc, tr.K,
+                               tr.Kp, tr.width[l], wc, nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0,
+                               (int)ngroup, out);
         } else {
             hipLaunchKernelGGL(k_ops_het<float>, dim3(blocks(c * KpKp)), dim3(kB), 0, s, g, st8, tr.D, tr.nc, tr.K,
                                tr.Kp, tr.width[l], nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, c, out,
