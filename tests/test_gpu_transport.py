@@ -74,3 +74,19 @@ def test_transport_rejects_non_unit_directions(ev):
         with pytest.raises(ev.ErtError) as ei:
             plan.transport(None, to_dev(case["f"]), np.array([[1.0, 0.1]]), phi)
         assert ei.value.status == ev.EINVAL
+
+
+@pytest.mark.parametrize("n,scale", [((17, 8, 5), 1.0), ((9, 9, 9), 10.0), ((1, 9, 33), 100.0), ((70, 3, 2), 10.0),
+                                     ((2, 2), 1.0), ((33, 17), 10.0), ((1, 70), 100.0), ((65, 40), 1.0)])
+def test_transport_tiles_and_step_ranges(ev, n, scale):
+    """Grids around and below a tile of cells (thin ones too), independent cell values, steps of
+    an optical depth about 0.05, 0.5 and 5 (the three ranges of the step's integral)."""
+    N, h = int(np.prod(n)), 0.1
+    rng = np.random.default_rng(N)
+    st = scale * rng.uniform(0.5, 1.5, N)
+    case = {"dim": len(n), "n": n, "h": h, "kernel": 1, "sigma_t": st, "sigma_s": 0.9 * st, "f": rng.uniform(0, 1, N)}
+    U = rng.uniform(0, 1, N)
+    dirs = _dirs(len(n), 3, 4)
+    got = _run(ev, case, U, case["f"], dirs)
+    ref = T.recover(U, case["f"], st, 0.9 * st, n, h, dirs)
+    assert max(rel_l2(got[k], ref[:, k]) for k in range(len(dirs))) <= 1e-12
