@@ -2692,6 +2692,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
             a.ntarget = tr.nleaf;
             a.B = nrhs;
             a.M = tr.S;
+            a.used = tr.S;
             a.nsrc = tr.nleaf;
             a.W = q;
             a.stage = stage_near;
@@ -2778,6 +2779,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
                 a.ntarget = tr.nbox[l];
                 a.B = nrhs;
                 a.M = tr.Kp;
+                a.used = tr.K;
                 a.nsrc = tr.nbox[l];
                 a.W = W[l];
                 a.stage = stage;

@@ -236,6 +236,7 @@ struct PairStream {
     size_t rows;             // right-hand sides it holds: pair_rows(), or (FP64) at least kPairStreamRhs
     void* L;                 // [B][ntarget][M]
     int accumulate;
+    int used;                // rows and columns of a block past these are zero (padding; M: none)
     // stage timing (ert_vie_profile): the pair products under prof_stage, their
     // per-target sums under ERT_STAGE_REDUCE; null when not profiling
     Profiler* prof = nullptr;

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void k_pair_sym(PairStream g, int b0, int R, i
     constexpr int NWD = VEC == 4 ? (SPLIT ? 8 : 4) : CPL;
     constexpr int ESZ = F32 ? 4 : 2;                    // bytes per stored value and plane
     extern __shared__ __align__(16) unsigned char smem[];
-    const int M = g.M;
+    const int M = g.M, used = g.used;                   // the padding is not read
     T* wb = (T*)smem;                                   // [RB][MP] forward sources (box b)
     T* wa = wb + RB * MP;                               // [RB][MP] backward sources (box a)
     T* bacc = wa + RB * MP;                             // [RB][MP] backward sums
@@ -150,9 +150,9 @@ __global__ __launch_bounds__(256) void k_pair_sym(PairStream g, int b0, int R, i
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) {
             const int j = j0 + r;
-            const bool ok = t < nstep && r < R && j < M;
+            const bool ok = t < nstep && r < R && j < used;
             if constexpr (VEC == 4) {
-                const unsigned off = ok && i0 < M ? (unsigned)(((size_t)j * M + i0) * ESZ) : kBufOob;
+                const unsigned off = ok && i0 < used ? (unsigned)(((size_t)j * M + i0) * ESZ) : kBufOob;
                 typedef unsigned v4u __attribute__((ext_vector_type(4)));
                 const v4u h = __builtin_amdgcn_raw_buffer_load_b128(rs0, off, 0, 0);
                 v[r][0] = h[0]; v[r][1] = h[1]; v[r][2] = h[2]; v[r][3] = h[3];
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void k_pair_sym(PairStream g, int b0, int R, i
             } else {
 #pragma unroll
                 for (int e = 0; e < CPL; ++e) {
-                    const unsigned off = ok && i0 + e < M ? (unsigned)(((size_t)j * M + i0 + e) * ESZ) : kBufOob;
+                    const unsigned off = ok && i0 + e < used ? (unsigned)(((size_t)j * M + i0 + e) * ESZ) : kBufOob;
                     if constexpr (F32) {
                         v[r][e] = __builtin_amdgcn_raw_buffer_load_b32(rs0, off, 0, 0);
                     } else {
@@ -883,8 +883,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
 // Per-target sums of the staging rows (rhs b0..b0+nb-1), over the target's
 // contiguous directed rows in order, skipping rows of pairs that do not exist.
+// Bound: the staging rows' traffic; eight rows are in flight per thread (one at a time,
+// behind its index: 48^3, order 6, the three sums of an apply 127 -> 50 us).
 template <typename T>
-__global__ void k_pair_reduce(PairStream g, int b0, int nb)
+__global__ __launch_bounds__(256) void k_pair_reduce(PairStream g, int b0, int nb)
 {
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     const long per = g.ntarget * g.M;
@@ -894,10 +896,21 @@ __global__ void k_pair_reduce(PairStream g, int b0, int nb)
     const long t = rem / g.M;
     const int r = (int)(rem - t * g.M);
     const T* St = (const T*)g.stage + (long)b * g.nrows * g.M + r;
-    const long k1 = g.tstart[t + 1];
+    const long k0 = g.tstart[t], k1 = g.tstart[t + 1];
     T sum = T(0);
-    for (long k = g.tstart[t]; k < k1; ++k)
-        if (!g.row_src || g.row_src[k] >= 0) sum += St[k * g.M];
+    for (long k = k0; k < k1; k += 8) {
+        T v[8];
+        bool in[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            in[u] = k + u < k1;
+            if (g.row_src) in[u] = in[u] && g.row_src[in[u] ? k + u : k0] >= 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = St[(in[u] ? k + u : k0) * g.M];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += in[u] ? v[u] : T(0);
+    }
     T* d = (T*)g.L + (long)(b0 + b) * per + rem;
     *d = g.accumulate ? *d + sum : sum;
 }
