@@ -22,6 +22,9 @@
 // The symbol is built once in FP64 by the same line kernels on the full
 // periodic grid (w has no zero padding) and folded to its distinct values
 // (c is even along every axis): 1/c on (m2/2 + 1) x (m1/2 + 1) x H0, FP32.
+// Bound: the latency of a stage (LDS, barrier) and of the launches.  The radix 2, 4 and 8
+// butterflies are sums in registers (as matrices of roots read from LDS they took 64
+// complex products each): 512^2 49 -> 38 us, 64^3 74 -> 57 us, 48 x 60 32 -> 17.5 us.
 #include "common.hpp"
 
 #include <algorithm>
@@ -55,6 +58,11 @@ namespace {
 constexpr int kThreads = 256;
 constexpr size_t kLdsMax = 64 * 1024;
 constexpr int kMaxPeriod = 1024;
+// Lines per workgroup: 16 (whole lines of memory across the axis), fewer while a workgroup
+// takes more than a fifth of a CU's LDS or there are fewer than two workgroups per CU.
+// 96^3 (periods of 192): 16 lines in 60 KB 152 us, 8 lines 111 us; 100 x 264: 31 and 23 us.
+constexpr size_t kLdsWant = 32 * 1024;
+constexpr long kMinGroups = 512;
 
 // Smallest integer >= 2 n with no prime factor above 7.
 int smooth_period(int n)
@@ -82,7 +90,7 @@ int factorize(int m, int* f)
 // i at base + a * sa + b * sb + i * si (source) and likewise for the destination.
 struct Lines {
     int m, nin, nout;
-    int A, B, TX;
+    int A, B, LTX;               // lines per workgroup: 2^LTX
     long sa, sb, si;
     long da, db, di;
     int nfac;
@@ -103,30 +111,99 @@ __device__ __forceinline__ Cx<R> twmul(Cx<R> x, Cx<R> w, bool inv)
     return {x.re * w.re - x.im * wi, x.re * wi + x.im * w.re};
 }
 
-template <typename R, int RAD>
-__device__ void fft_stage(const Cx<R>* __restrict__ in, Cx<R>* __restrict__ out, const Cx<R>* __restrict__ tw,
-                          int m, int p, int TX, int TXP, bool inv)
+// x times i (inverse) or -i (forward): `sg` 1 or -1.
+template <typename R>
+__device__ __forceinline__ Cx<R> rot(Cx<R> x, R sg)
 {
-    const int mr = m / RAD, step = m / (p * RAD);
-    for (int e = threadIdx.x; e < TX * mr; e += kThreads) {
-        const int t = e % TX, j = e / TX, k = j % p;
-        Cx<R> x[RAD];
+    return {-sg * x.im, sg * x.re};
+}
+template <typename R>
+__device__ __forceinline__ Cx<R> add(Cx<R> a, Cx<R> b)
+{
+    return {a.re + b.re, a.im + b.im};
+}
+template <typename R>
+__device__ __forceinline__ Cx<R> sub(Cx<R> a, Cx<R> b)
+{
+    return {a.re - b.re, a.im - b.im};
+}
+
+// DFT of four values, two apart in v (stride ST), in place and in order.
+template <typename R, int ST>
+__device__ __forceinline__ void dft4(Cx<R>* v, R sg)
+{
+    const Cx<R> a = add(v[0], v[2 * ST]), b = sub(v[0], v[2 * ST]);
+    const Cx<R> c = add(v[ST], v[3 * ST]), d = rot(sub(v[ST], v[3 * ST]), sg);
+    v[0] = add(a, c);
+    v[ST] = add(b, d);
+    v[2 * ST] = sub(a, c);
+    v[3 * ST] = sub(b, d);
+}
+
+// DFT of RAD values in registers.  2, 4 and 8 by halving (adds, and four products by
+// sqrt(1/2)); 3, 5 and 7 as the matrix of roots, from the twiddles.
+template <typename R, int RAD>
+__device__ __forceinline__ void dft(Cx<R> (&x)[RAD], const Cx<R>* __restrict__ tw, int mr, bool inv)
+{
+    const R sg = inv ? R(1) : R(-1);
+    if constexpr (RAD == 2) {
+        const Cx<R> a = x[0];
+        x[0] = add(a, x[1]);
+        x[1] = sub(a, x[1]);
+    } else if constexpr (RAD == 4) {
+        dft4<R, 1>(x, sg);
+    } else if constexpr (RAD == 8) {
+        dft4<R, 2>(x, sg);                             // even and odd halves
+        dft4<R, 2>(x + 1, sg);
+        const R h = R(0.70710678118654752440);
+        const Cx<R> e[4] = {x[0], x[2], x[4], x[6]};
+        const Cx<R> o1 = rot(x[3], sg), o3 = rot(x[7], sg);
+        const Cx<R> o[4] = {x[1],
+                            {h * (x[3].re + o1.re), h * (x[3].im + o1.im)},
+                            rot(x[5], sg),
+                            {h * (o3.re - x[7].re), h * (o3.im - x[7].im)}};
 #pragma unroll
-        for (int q = 0; q < RAD; ++q) x[q] = in[(j + q * mr) * TXP + t];
-#pragma unroll
-        for (int q = 1; q < RAD; ++q) x[q] = twmul(x[q], tw[q * k * step], inv);   // q k step < m
-        const int base = (j - k) * RAD + k;
+        for (int k = 0; k < 4; ++k) {
+            x[k] = add(e[k], o[k]);
+            x[k + 4] = sub(e[k], o[k]);
+        }
+    } else {
+        Cx<R> y[RAD];
 #pragma unroll
         for (int s = 0; s < RAD; ++s) {
-            Cx<R> acc = x[0];
+            y[s] = x[0];
 #pragma unroll
-            for (int q = 1; q < RAD; ++q) {
-                const Cx<R> v = twmul(x[q], tw[((q * s) % RAD) * mr], inv);
-                acc.re += v.re;
-                acc.im += v.im;
-            }
-            out[(base + s * p) * TXP + t] = acc;
+            for (int q = 1; q < RAD; ++q) y[s] = add(y[s], twmul(x[q], tw[((q * s) % RAD) * mr], inv));
         }
+#pragma unroll
+        for (int s = 0; s < RAD; ++s) x[s] = y[s];
+    }
+}
+
+// Position of element i of a line in LDS: a gap every eight, so that the first stage's
+// stores, eight elements apart from thread to thread, spread over the banks.
+__host__ __device__ __forceinline__ int slot(int i) { return i + (i >> 3); }
+
+template <typename R, int RAD>
+__device__ void fft_stage(const Cx<R>* __restrict__ in, Cx<R>* __restrict__ out, const Cx<R>* __restrict__ tw,
+                          int m, int p, int LTX, int TXP, bool inv)
+{
+    const int mr = m / RAD, step = m / (p * RAD);
+    const float inv_p = 1.0f / (float)p;
+    for (int e = threadIdx.x; e < mr << LTX; e += kThreads) {
+        const int t = e & ((1 << LTX) - 1), j = e >> LTX;
+        const int k = j - (int)(((float)j + 0.5f) * inv_p) * p;      // j mod p (j < 1024)
+        Cx<R> x[RAD];
+#pragma unroll
+        for (int q = 0; q < RAD; ++q) x[q] = in[slot(j + q * mr) * TXP + t];
+        if (p > 1) {
+#pragma unroll
+            for (int q = 1; q < RAD; ++q) x[q] = twmul(x[q], tw[q * k * step], inv);   // q k step < m
+        }
+        dft<R, RAD>(x, tw, mr, inv);
+        const int base = (j - k) * RAD + k;
+#pragma unroll
+        for (int s = 0; s < RAD; ++s) out[slot(base + s * p) * TXP + t] = x[s];
     }
 }
 
@@ -138,12 +215,12 @@ __device__ Cx<R>* fft_lines(Cx<R>* a, Cx<R>* b, const Cx<R>* tw, const Lines& L,
     for (int s = 0; s < L.nfac; ++s) {
         const int r = L.fac[s];
         switch (r) {
-        case 8: fft_stage<R, 8>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
-        case 4: fft_stage<R, 4>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
-        case 2: fft_stage<R, 2>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
-        case 3: fft_stage<R, 3>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
-        case 5: fft_stage<R, 5>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
-        default: fft_stage<R, 7>(a, b, tw, L.m, p, L.TX, TXP, inv); break;
+        case 8: fft_stage<R, 8>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
+        case 4: fft_stage<R, 4>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
+        case 2: fft_stage<R, 2>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
+        case 3: fft_stage<R, 3>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
+        case 5: fft_stage<R, 5>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
+        default: fft_stage<R, 7>(a, b, tw, L.m, p, L.LTX, TXP, inv); break;
         }
         __syncthreads();
         Cx<R>* t = a;
@@ -165,10 +242,10 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
                                                     const Cx<R>* __restrict__ tw)
 {
     extern __shared__ unsigned char lds_raw[];
-    const int m = L.m, TX = L.TX, TXP = TX == 1 ? 1 : TX + 1;
+    const int m = L.m, LTX = L.LTX, TX = 1 << LTX, TXP = TX == 1 ? 1 : TX + 1;
     Cx<R>* tws = reinterpret_cast<Cx<R>*>(lds_raw);
     Cx<R>* b0 = tws + m;
-    Cx<R>* b1 = b0 + (size_t)m * TXP;
+    Cx<R>* b1 = b0 + (size_t)slot(m) * TXP;
     const int tiles = (L.A + TX - 1) / TX;
     const int a0 = (int)(blockIdx.x % tiles) * TX;
     const long b = blockIdx.x / tiles;
@@ -178,9 +255,10 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
     // load (zeros beyond nin and for missing lines)
     const bool rows = L.si == 1;          // lines run along the contiguous axis
     const long sbase = a0 * L.sa + b * L.sb;
+    const float inv_m = 1.0f / (float)m, inv_n = 1.0f / (float)L.nout;    // e / m, e / nout (e < 16384)
     for (int e = threadIdx.x; e < TX * m; e += kThreads) {
-        const int i = rows ? e % m : e / TX;
-        const int t = rows ? e / m : e % TX;
+        const int t = rows ? (int)(((float)e + 0.5f) * inv_m) : e & (TX - 1);
+        const int i = rows ? e - t * m : e >> LTX;
         Cx<R> v = {R(0), R(0)};
         if (t < tv && i < L.nin) {
             const long off = sbase + t * L.sa + i * L.si;
@@ -190,16 +268,16 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
                 v = static_cast<const Cx<R>*>(src_)[off];
             }
         }
-        b0[i * TXP + t] = v;
+        b0[slot(i) * TXP + t] = v;
     }
     __syncthreads();
     if (MODE == kInvReal) {
         // X[k] = conj(X[m - k]) above the stored half
         for (int e = threadIdx.x; e < TX * m; e += kThreads) {
-            const int i = e / TX, t = e % TX;
+            const int i = e >> LTX, t = e & (TX - 1);
             if (i >= L.nin) {
-                Cx<R> v = b0[(m - i) * TXP + t];
-                b0[i * TXP + t] = {v.re, -v.im};
+                Cx<R> v = b0[slot(m - i) * TXP + t];
+                b0[slot(i) * TXP + t] = {v.re, -v.im};
             }
         }
         __syncthreads();
@@ -209,10 +287,10 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
     if (MODE == kMid) {
         const long fb = L.mb > 0 ? fold((int)b, L.mb) : b;
         for (int e = threadIdx.x; e < TX * m; e += kThreads) {
-            const int i = e / TX, t = e % TX;
+            const int i = e >> LTX, t = e & (TX - 1);
             const R s = (t < tv) ? (R)L.invc[fold(i, m) * L.ci + fb * L.cb + (a0 + t) * L.ca] : R(0);
-            Cx<R> v = res[i * TXP + t];
-            res[i * TXP + t] = {v.re * s, v.im * s};
+            Cx<R> v = res[slot(i) * TXP + t];
+            res[slot(i) * TXP + t] = {v.re * s, v.im * s};
         }
         __syncthreads();
         Cx<R>* other = res == b0 ? b1 : b0;
@@ -223,11 +301,11 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
     const long dbase = a0 * L.da + b * L.db;
     const bool drows = L.di == 1;
     for (int e = threadIdx.x; e < TX * L.nout; e += kThreads) {
-        const int i = drows ? e % L.nout : e / TX;
-        const int t = drows ? e / L.nout : e % TX;
+        const int t = drows ? (int)(((float)e + 0.5f) * inv_n) : e & (TX - 1);
+        const int i = drows ? e - t * L.nout : e >> LTX;
         if (t >= tv) continue;
         const long off = dbase + t * L.da + i * L.di;
-        const Cx<R> v = res[i * TXP + t];
+        const Cx<R> v = res[slot(i) * TXP + t];
         if (MODE == kInvReal)
             static_cast<double*>(dst_)[off] = (double)v.re * L.scale;
         else
@@ -348,27 +426,21 @@ template <typename R>
 size_t lds_bytes(int m, int TX)
 {
     const int TXP = TX == 1 ? 1 : TX + 1;
-    return sizeof(Cx<R>) * (size_t)m * (1 + 2 * (size_t)TXP);
-}
-
-template <typename R>
-int lines_per_group(int m)
-{
-    int TX = 16;
-    while (TX > 1 && lds_bytes<R>(m, TX) > kLdsMax) TX /= 2;
-    return TX;
+    return sizeof(Cx<R>) * ((size_t)m + 2 * (size_t)slot(m) * TXP);
 }
 
 template <typename R, int MODE, bool INV>
 ert_status launch_lines(hipStream_t s, Lines L, const void* src, void* dst, const Cx<R>* tw)
 {
-    L.TX = lines_per_group<R>(L.m);
-    const size_t lds = lds_bytes<R>(L.m, L.TX);
+    L.LTX = 4;
+    while (L.LTX > 0 && lds_bytes<R>(L.m, 1 << L.LTX) > kLdsWant) --L.LTX;
+    while (L.LTX > (L.si == 1 || L.di == 1 ? 0 : 2) && (long)((L.A + (1 << L.LTX) - 1) >> L.LTX) * L.B < kMinGroups) --L.LTX;
+    const size_t lds = lds_bytes<R>(L.m, 1 << L.LTX);
     if (lds > kLdsMax) {
         record_error("ert_vie_fft_precond: line transform does not fit in LDS");
         return ERT_EUNSUPPORTED;
     }
-    const long tiles = (L.A + L.TX - 1) / L.TX;
+    const long tiles = (L.A + (1 << L.LTX) - 1) >> L.LTX;
     const long blocks = tiles * L.B;
     if (blocks <= 0) return ERT_OK;
     if (blocks > 0x7fffffffL) return ERT_EUNSUPPORTED;
