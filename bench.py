@@ -349,9 +349,9 @@ C5_CHEB, C5_INNER_CHEB = 6, 4
 # (workload, precision, stage of the kernel, execution forms); a combination without counters,
 # or a kernel changed since they were taken, reports null.
 MEASURED_TRAFFIC = dict(MEASURED_TRAFFIC)
-# 128^3 FP64 operator (k_pair_sym over the symmetric caches): far field 66.13 GB per apply in
+# 128^3 FP64 operator (k_pair_sym over the symmetric caches): far field 63.84 GB per apply in
 # 3 launches, near field 53.95 GB in one (profiles/pair_sym_c5_128cubed_hbm_traffic.md)
-MEASURED_TRAFFIC[("c5_128", "fp64", "m2l")] = 22.044e9
+MEASURED_TRAFFIC[("c5_128", "fp64", "m2l")] = 21.280e9
 MEASURED_TRAFFIC[("c5_128", "fp64", "near")] = 53.948e9
 
 
@@ -376,17 +376,17 @@ def het_roofline(info, stage_ms, launches, n, near_plane_bytes=4, workload=None)
     so one block is stored per unordered pair of boxes and serves both directions.
     Algorithmic bytes: near field, the S x S block of every leaf with itself and one block per
     unordered pair of neighbouring leaves (grid of whole leaves), near_plane_bytes per value;
-    far field, one Kp x Kp FP32 matrix per unordered interaction-list pair of every level.  The
-    dominant stage (near or m2l) by time is the reported kernel; time per launch from the stage
-    events."""
-    Kp = info["nodes_padded"]
+    far field, the K x K FP32 values of one matrix per unordered interaction-list pair of every
+    level (the rows and columns that pad it are not read).  The dominant stage (near or m2l)
+    by time is the reported kernel; time per launch from the stage events."""
+    K = info["nodes"]
     S = info["leaf"] ** len(n)
     nb = [-(-v // info["leaf"]) for v in n]
     nleaf = int(np.prod(nb))
     directed = int(np.prod([3 * v - 2 for v in nb]))           # leaf pairs at offsets in [-1, 1]^d
     near_blocks = nleaf + (directed - nleaf) // 2
     near_bytes = near_blocks * S * S * near_plane_bytes
-    far_bytes = sum(info["far_pairs"][l] // 2 * Kp * Kp * 4.0 for l in range(2, info["levels"] + 1))
+    far_bytes = sum(info["far_pairs"][l] // 2 * K * K * 4.0 for l in range(2, info["levels"] + 1))
     cand = {"near": (near_bytes, stage_ms.get("near", 0.0), launches.get("near", 1.0)),
             "m2l": (far_bytes, stage_ms.get("m2l", 0.0), launches.get("m2l", 1.0))}
     dom = max(cand, key=lambda k: cand[k][1])
