@@ -1017,8 +1017,8 @@ __global__ void k_ops_het(Geo g, const double* __restrict__ st8, int D, int nc, 
 }
 
 
-// The same matrices (3D) with sigma_t read from LDS.  A workgroup takes kOpsRays x
-// kOpsThreads entries of one pair and marches them window by window in the ray
+// The same matrices (3D) with sigma_t read from LDS.  A workgroup takes RAYS x
+// THREADS entries of one pair and marches them window by window in the ray
 // parameter: window i holds, for a ray of m steps, the samples q in (i m / nwin,
 // (i + 1) m / nwin].  Their points lie in the box swept by (1 - f) A + f B for f in
 // [i / nwin - 1/(2m), (i + 1) / nwin] (A, B the two boxes; the shift below i / nwin is
@@ -1032,32 +1032,41 @@ __global__ void k_ops_het(Geo g, const double* __restrict__ st8, int D, int nc, 
 // nodes first: their cells at a time lie in one or two rows of the box, shared or on
 // different banks (simulated with these pitches 1.08 cycles per 16 lanes; 1.9 with the
 // target's nodes in order and pitches of 18).  48^3, order 6: 59 -> 37 ms.
-constexpr int kOpsThreads = 512;
-constexpr int kOpsRays = 8;
-constexpr int kOpsSide = 21;                       // cells per axis of a staged box
-constexpr int kOpsRow = 21, kOpsPlane = 460;       // LDS pitch of a row and a plane
+// Boxes of 15 to 18 cells a side take staged boxes of 27, the whole LDS of a CU, in one
+// workgroup of twice the threads: the 16-cell boxes of 48^3 in 1.9 ms, 3.9 ms by gathers
+// from the corner table.
 constexpr int kOpsMaxSteps = 255;
+template <int SIDE_, int PLANE_, int THREADS_, int RAYS_>
+struct OpsForm {
+    static constexpr int SIDE = SIDE_;                 // cells per axis of a staged box
+    static constexpr int ROW = SIDE_, PLANE = PLANE_;  // LDS pitch of a row and a plane
+    static constexpr int THREADS = THREADS_, RAYS = RAYS_;
+};
+using OpsSmall = OpsForm<21, 460, 512, 8>;
+using OpsWide = OpsForm<27, 744, 1024, 4>;
 
 // Windows of a pair of boxes of wc cells a side, omax boxes apart: the fewest whose staged
-// boxes fit; 0 when none up to 32 do.
-__host__ __device__ inline int ops_windows(int wc, int omax)
+// boxes of `side` cells fit; 0 when none up to 32 do or a ray may have too many steps
+// (3.47 wc (omax + 1): half a cell each, to the far corners).
+__host__ __device__ inline int ops_windows(int side, int wc, int omax)
 {
+    if (3.47 * wc * (omax + 1) + 1.0 > kOpsMaxSteps) return 0;
     for (int nw = 1; nw <= 32; ++nw)
-        if (wc + (omax * wc + nw - 1) / nw + 5 <= kOpsSide) return nw;
+        if (wc + (omax * wc + nw - 1) / nw + 5 <= side) return nw;
     return 0;
 }
 
 // one copy of the integral for the rays of a thread
 __device__ __noinline__ double far_cell_int(double d0, double d1, double d2) { return cell_int(3, d0, d1, d2, 64.0); }
 
-template <typename T, bool MII>
-__global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
+template <typename T, bool MII, typename FORM>
+__global__ __launch_bounds__(FORM::THREADS, 4) void k_ops_het_lds(
     Geo g, const double* __restrict__ st, int nc, int K, int Kp, double w, int wc, int nl0, int nl1, int nl2,
     const double* __restrict__ cheb, const int* __restrict__ pair_t, const int* __restrict__ pair_s, long p0, int ngroup,
     T* __restrict__ opsT)
 {
-    constexpr int R = kOpsRays;
-    __shared__ double sl[(kOpsSide - 1) * (kOpsPlane + kOpsRow) + kOpsSide];
+    constexpr int R = FORM::RAYS, NT = FORM::THREADS, SIDE = FORM::SIDE, ROW = FORM::ROW, PLANE = FORM::PLANE;
+    __shared__ double sl[(SIDE - 1) * (PLANE + ROW) + SIDE];
     __shared__ double inv[kOpsMaxSteps + 1];
     __shared__ double X[3][8], Y[3][8];            // node coordinates of the two boxes
     const long pl = blockIdx.x / ngroup;
@@ -1071,8 +1080,8 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
     const int n[3] = {g.n0, g.n1, g.n2};
     int omax = 0;
     for (int a = 0; a < 3; ++a) omax = abs(sb[a] - tb[a]) > omax ? abs(sb[a] - tb[a]) : omax;
-    const int nwin = ops_windows(wc, omax);
-    for (int i = tid; i <= kOpsMaxSteps; i += kOpsThreads) inv[i] = 1.0 / double(i);
+    const int nwin = ops_windows(SIDE, wc, omax);
+    for (int i = tid; i <= kOpsMaxSteps; i += NT) inv[i] = 1.0 / double(i);
     if (tid < 3 * nc) {
         const int a = tid / nc, i = tid - a * nc;
         X[a][i] = node_coord(w, tb[a], cheb[i]);
@@ -1093,7 +1102,7 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
     };
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int e = gi * (R * kOpsThreads) + j * kOpsThreads + tid;
+        const int e = gi * (R * NT) + j * NT + tid;
         rs[j] = 0.0;
         ray[j] = 0;
         if (e < K * K) {
@@ -1120,7 +1129,7 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
             const double hi_pos = (l0 > l1 ? l0 : l1) + w;
             kmin[a] = (int)floor(lo_pos * inv_h - 0.5) - 1;
             const int e = (int)floor(hi_pos * inv_h - 0.5) + 3 - kmin[a];
-            ext[a] = e < kOpsSide ? e : kOpsSide;
+            ext[a] = e < SIDE ? e : SIDE;
         }
         __syncthreads();  // the previous window's reads are done
         {
@@ -1130,12 +1139,12 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
             const float inv_ext = 1.0f / (float)ext[1];
             if (x < ext[0])
 #pragma unroll 4
-                for (int row = tid >> 5; row < ext[1] * ext[2]; row += kOpsThreads / 32) {
+                for (int row = tid >> 5; row < ext[1] * ext[2]; row += NT / 32) {
                     const int z = (int)(((float)row + 0.5f) * inv_ext), y = row - z * ext[1];
                     const int cy = kmin[1] + y, cz = kmin[2] + z;
                     const long c1 = cy < 0 ? 0 : (cy > n[1] - 1 ? n[1] - 1 : cy);
                     const long c2 = cz < 0 ? 0 : (cz > n[2] - 1 ? n[2] - 1 : cz);
-                    sl[x + kOpsRow * y + kOpsPlane * z] = st[c0 + n[0] * (c1 + n[1] * c2)];
+                    sl[x + ROW * y + PLANE * z] = st[c0 + n[0] * (c1 + n[1] * c2)];
                 }
         }
         __syncthreads();
@@ -1157,11 +1166,11 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
                 const double u0 = fma(q, e0, a0), u1 = fma(q, e1, a1), u2 = fma(q, e2, a2);
                 const double k0 = floor(u0), k1 = floor(u1), k2 = floor(u2);
                 const double t0 = u0 - k0, t1 = u1 - k1, t2 = u2 - k2;
-                const double* c = sl + (int)fma(double(kOpsPlane), k2, fma(double(kOpsRow), k1, k0));
+                const double* c = sl + (int)fma(double(PLANE), k2, fma(double(ROW), k1, k0));
                 const double c00 = fma(t0, c[1] - c[0], c[0]);
-                const double c10 = fma(t0, c[kOpsRow + 1] - c[kOpsRow], c[kOpsRow]);
-                const double c01 = fma(t0, c[kOpsPlane + 1] - c[kOpsPlane], c[kOpsPlane]);
-                const double c11 = fma(t0, c[kOpsPlane + kOpsRow + 1] - c[kOpsPlane + kOpsRow], c[kOpsPlane + kOpsRow]);
+                const double c10 = fma(t0, c[ROW + 1] - c[ROW], c[ROW]);
+                const double c01 = fma(t0, c[PLANE + 1] - c[PLANE], c[PLANE]);
+                const double c11 = fma(t0, c[PLANE + ROW + 1] - c[PLANE + ROW], c[PLANE + ROW]);
                 const double c0 = fma(t1, c10 - c00, c00), c1 = fma(t1, c11 - c01, c01);
                 s += fma(t2, c1 - c0, c0);
             }
@@ -1172,7 +1181,7 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
     T* out = opsT + pl * (long)Kp * Kp;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int e = gi * (R * kOpsThreads) + j * kOpsThreads + tid;
+        const int e = gi * (R * NT) + j * NT + tid;
         if (e >= K * K) continue;
         const unsigned nd = ray[j];
         const double r2 = dist2(nd), tau = sqrt(r2) * inv[nd >> 24] * rs[j];
@@ -1190,7 +1199,7 @@ __global__ __launch_bounds__(kOpsThreads, 4) void k_ops_het_lds(
     }
     // the padding of the matrix
     if (gi == 0 && Kp > K)
-        for (int i = tid; i < Kp * Kp; i += kOpsThreads)
+        for (int i = tid; i < Kp * Kp; i += NT)
             if (i % Kp >= K || i / Kp >= K) out[i] = T(0);
 }
 
@@ -1966,18 +1975,25 @@ ert_status het_fill(ert_plan_impl* p, hipStream_t s, const FmmTree& tr, const do
     const long pchunk = std::max<long>(1, (1L << 27) / KpKp);
     const Geo& g = p->geo;
     const int nl[3] = {tr.nl[l][0], tr.nl[l][1], tr.nl[l][2]};
-    // wide boxes (16 cells a side and more) do not fit in LDS with the cells between them
+    // the boxes and the cells between them in LDS up to 18 cells a side, the corner table beyond
     const int wc = tr.leaf << (tr.L - l);
-    const bool lds = tr.D == 3 && ops_windows(wc, 3) > 0;
-    const long ngroup = ((long)tr.K * tr.K + kOpsRays * kOpsThreads - 1) / (kOpsRays * kOpsThreads);
+    const bool small = tr.D == 3 && ops_windows(OpsSmall::SIDE, wc, 3) > 0;
+    const bool wide = tr.D == 3 && !small && ops_windows(OpsWide::SIDE, wc, 3) > 0;
+    const auto groups = [&](long per) { return (int)(((long)tr.K * tr.K + per - 1) / per); };
     for (long q0 = p0; q0 < p0 + cnt; q0 += pchunk) {
         const long c = std::min(pchunk, p0 + cnt - q0);
         float* out = dst + (size_t)(q0 - p0) * KpKp;
-        if (lds) {
-            auto kern = p->o.scheme ? k_ops_het_lds<float, true> : k_ops_het_lds<float, false>;
-            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(kOpsThreads), 0, s, g, p->d_st, tr.nc, tr.K,
-                               tr.Kp, tr.width[l], wc, nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0,
-                               (int)ngroup, out);
+        auto launch = [&](auto kern, int threads, int rays) {
+            const int ngroup = groups((long)threads * rays);
+            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(threads), 0, s, g, p->d_st, tr.nc, tr.K, tr.Kp,
+                               tr.width[l], wc, nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, ngroup, out);
+        };
+        if (small) {
+            launch(p->o.scheme ? k_ops_het_lds<float, true, OpsSmall> : k_ops_het_lds<float, false, OpsSmall>,
+                   OpsSmall::THREADS, OpsSmall::RAYS);
+        } else if (wide) {
+            launch(p->o.scheme ? k_ops_het_lds<float, true, OpsWide> : k_ops_het_lds<float, false, OpsWide>,
+                   OpsWide::THREADS, OpsWide::RAYS);
         } else {
             hipLaunchKernelGGL(k_ops_het<float>, dim3(blocks(c * KpKp)), dim3(kB), 0, s, g, st8, tr.D, tr.nc, tr.K,
                                tr.Kp, tr.width[l], nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, c, out,

@@ -54,7 +54,7 @@ def test_near_blocks(ev, oracle_mod, n, h, leaf, scheme):
 
 
 @pytest.mark.parametrize("n,leaf,scheme", [((37, 1, 21), 8, 0), ((19, 30, 18), 4, 0), ((25, 17, 9), 5, 1), ((40, 9, 2), 8, 0),
-                                           ((14, 27, 13), 7, 0)])
+                                           ((14, 27, 13), 7, 0), ((66, 9, 5), 4, 0), ((70, 8, 9), 6, 1)])
 def test_far_blocks_staged(ev, oracle_mod, n, leaf, scheme):
     """Far blocks from staged boxes: ragged grids and grids one or two cells thick, boxes
     that reach past the grid (nodes outside take the face values).  Smooth medium, eight
