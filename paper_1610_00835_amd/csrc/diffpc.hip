@@ -207,7 +207,7 @@ __global__ void k_prolong_add(int f0, int f1, int f2, double* __restrict__ Uf, i
 
 // ------------------------------------------------------------- 2D tiles ----
 
-// One half of a cycle on a 2D level.  A workgroup owns a kTile x kTile tile and holds
+// One half of a cycle on a 2D level.  A workgroup owns a TILE x TILE tile and holds
 // the tile and a halo of kHalo cells in LDS (iterate) and registers (right-hand side
 // and coefficients of its cells).  The four half-sweeps run on the whole box; a
 // half-sweep spoils one more ring of cells, counted from the box's edge, and the
@@ -218,17 +218,28 @@ __global__ void k_prolong_add(int f0, int f1, int f2, double* __restrict__ Uf, i
 //   up (UP = true): U_out = smooth(U_in + prolong(Ec)); with r, U_out receives
 //     r + that (the preconditioner's output; r and U_out may be the same buffer).
 // Neighbouring tiles read each other's U_in, so U_out is another buffer.
-// Bound: launch latency and the four barriers (2D 264^2: 81 workgroups, 7 cells per
-// thread); 32 x 32 tiles keep the halo's share at 1.7.
-constexpr int kTile = 32, kHalo = 5, kBox = kTile + 2 * kHalo, kPitch = kBox + 1;
-constexpr int kBoxPer = (kBox * kBox + 255) / 256;
+// Bound: launch latency, the load of a cell's nine values and the four barriers.  Tiles of 16
+// cells, one cell of the box per thread, spread a level over the chip: 264^2, 66 us per
+// application (20 launches); 86 us with tiles of 32 and two cells per thread, 150 us with
+// seven.  The larger tile pays where a level has more of them than the chip holds at once
+// (2048^2: 414 against 562 us): its halo doubles a cell's traffic instead of tripling it.
+constexpr int kHalo = 5;
+constexpr long kLargeLevel = 400000;              // cells
+template <int TILE_, int THREADS_>
+struct TileForm {
+    static constexpr int TILE = TILE_, THREADS = THREADS_;
+    static constexpr int BOX = TILE + 2 * kHalo, PITCH = BOX + 1, PER = (BOX * BOX + THREADS - 1) / THREADS;
+};
+using TileSmall = TileForm<16, 704>;
+using TileLarge = TileForm<32, 1024>;
 
-template <bool UP>
-__global__ __launch_bounds__(256) void k_tile(LvArgs a, const double* Uin, const double* Bin, const double* r,
+template <bool UP, typename F>
+__global__ __launch_bounds__(F::THREADS) void k_tile(LvArgs a, const double* Uin, const double* Bin, const double* r,
                                               const double* __restrict__ ss, int c0, int c1,
                                               const double* __restrict__ Ec, double* Uout, double* Bout,
                                               double* __restrict__ Bc)
 {
+    constexpr int kTile = F::TILE, kTileThreads = F::THREADS, kBox = F::BOX, kPitch = F::PITCH, kBoxPer = F::PER;
     __shared__ double u[kBox * kPitch];
     __shared__ double res[UP ? 1 : kTile * (kTile + 1)];
     const int tx0 = blockIdx.x * kTile, ty0 = blockIdx.y * kTile;
@@ -237,7 +248,7 @@ __global__ __launch_bounds__(256) void k_tile(LvArgs a, const double* Uin, const
     unsigned red = 0, upd = 0;                    // bit k: cell k is red, is updated by the sweeps
 #pragma unroll
     for (int k = 0; k < kBoxPer; ++k) {
-        const int e = threadIdx.x + 256 * k;
+        const int e = threadIdx.x + kTileThreads * k;
         const int ex = e % kBox, ey = e / kBox, x = tx0 + ex - kHalo, y = ty0 + ey - kHalo;
         const bool box = e < kBox * kBox;
         const bool in = box && x >= 0 && x < a.n0 && y >= 0 && y < a.n1;
@@ -274,7 +285,7 @@ __global__ __launch_bounds__(256) void k_tile(LvArgs a, const double* Uin, const
     }
 #pragma unroll
     for (int k = 0; k < kBoxPer; ++k) {
-        const int e = threadIdx.x + 256 * k;
+        const int e = threadIdx.x + kTileThreads * k;
         const int ex = e % kBox - kHalo, ey = e / kBox - kHalo, x = tx0 + ex, y = ty0 + ey;
         if (e >= kBox * kBox || ex < 0 || ex >= kTile || ey < 0 || ey >= kTile) continue;
         double rv = 0.0;
@@ -433,6 +444,14 @@ ert_status dense(hipStream_t s, DiffPc* d)
     return ERT_OK;
 }
 
+template <bool UP, typename F>
+void launch_tile(hipStream_t s, const LvArgs& a, const double* Uin, const double* B, const double* r, const double* ss,
+                 const DiffLevel& C, const double* Ec, double* Uout, double* Bout, double* Bc)
+{
+    const dim3 grid((unsigned)((a.n0 + F::TILE - 1) / F::TILE), (unsigned)((a.n1 + F::TILE - 1) / F::TILE));
+    hipLaunchKernelGGL((k_tile<UP, F>), grid, dim3(F::THREADS), 0, s, a, Uin, B, r, ss, C.n[0], C.n[1], Ec, Uout, Bout, Bc);
+}
+
 // One cycle from level k down in 2D.  first: the iterate starts at zero; r (finest level
 // only): the residual the preconditioner acts on; out: r + U instead of the level's V.
 ert_status vcycle2(hipStream_t s, DiffPc* d, int k, bool first, const double* r, double* out)
@@ -441,15 +460,13 @@ ert_status vcycle2(hipStream_t s, DiffPc* d, int k, bool first, const double* r,
     DiffLevel& L = d->lv[k];
     DiffLevel& C = d->lv[k + 1];
     const LvArgs a = args_of(d, L);
-    const dim3 grid((unsigned)((L.n[0] + kTile - 1) / kTile), (unsigned)((L.n[1] + kTile - 1) / kTile));
-    hipLaunchKernelGGL(k_tile<false>, grid, dim3(256), 0, s, a, first ? (const double*)nullptr : (const double*)L.V,
-                       (const double*)L.B, first ? r : nullptr, (const double*)L.ss, C.n[0], C.n[1],
-                       (const double*)nullptr, L.U, L.B, C.B);
+    const bool large = L.N >= kLargeLevel;
+    const auto down = large ? launch_tile<false, TileLarge> : launch_tile<false, TileSmall>;
+    const auto up = large ? launch_tile<true, TileLarge> : launch_tile<true, TileSmall>;
+    down(s, a, first ? nullptr : L.V, L.B, first ? r : nullptr, L.ss, C, nullptr, L.U, L.B, C.B);
     ERT_HIP(hipGetLastError());
     ERT_TRY(vcycle2(s, d, k + 1, true, nullptr, nullptr));
-    hipLaunchKernelGGL(k_tile<true>, grid, dim3(256), 0, s, a, (const double*)L.U, (const double*)L.B, out ? r : nullptr,
-                       (const double*)nullptr, C.n[0], C.n[1], (const double*)C.V, out ? out : L.V, (double*)nullptr,
-                       (double*)nullptr);
+    up(s, a, L.U, L.B, out ? r : nullptr, nullptr, C, C.V, out ? out : L.V, nullptr, nullptr);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }

@@ -41,7 +41,7 @@ def test_diff_precond_matches_reference(ev, name, n):
 
 
 # the edges of the forms: one dense level (512 cells, 2D and 3D, and one past it), tiles of
-# 32 with one, exact and ragged remainders, one-cell axes, several tiled levels
+# 16 with one, exact and ragged remainders, one-cell axes, several tiled levels
 @pytest.mark.parametrize("name,n", [("c1", (32, 16)), ("c1", (27, 19)), ("c5", (8, 8, 8)), ("c5", (9, 8, 8)),
                                     ("c1", (512, 1)), ("c1", (700, 1)), ("c1", (1, 33)), ("c3", (33, 47)),
                                     ("c3", (64, 32)), ("c3", (65, 97)), ("c3", (130, 250)), ("c5", (70, 1, 9))])
@@ -57,6 +57,19 @@ def test_diff_precond_forms(ev, name, n):
         ref = Dm.apply(R[:, k], case["dim"], case["n"], case["h"], case["sigma_t"], case["sigma_s"])
         assert rel_l2(Z[:, k], ref) <= 1e-12
     assert np.array_equal(z1, Z[:, 1])
+
+
+@pytest.mark.parametrize("n", [(650, 631), (1, 400001)])
+def test_diff_precond_large_levels(ev, n):
+    """A finest level past 400000 cells (tiles of 32), the others below; same bar."""
+    case = inputs.make_case("c1", n=n, seed=3)
+    N = int(np.prod(n))
+    st = np.random.default_rng(5).uniform(1.0, 9.0, N)
+    case.update(kernel=inputs.KERNEL_RAY, sigma_t=st, sigma_s=0.9 * st)
+    r = np.random.default_rng(4).standard_normal(N)
+    with ev.plan_from_case(case, method="direct", prec="fp64") as plan:
+        z = to_host(plan.diff_precond(to_dev(r), to_dev(np.zeros(N))))
+    assert rel_l2(z, Dm.apply(r, 2, case["n"], case["h"], st, 0.9 * st)) <= 1e-12
 
 
 def test_diff_precond_full_size(ev):
