@@ -150,14 +150,13 @@ __global__ __launch_bounds__(kBlk) void k_orth_final(const double* __restrict__ 
 }
 
 __global__ __launch_bounds__(kBlk) void k_gemv(const double* __restrict__ V, long ldv, int ncols,
-                                               const double* __restrict__ coef, double* __restrict__ w, long N,
-                                               double sign)
+                                               const double* __restrict__ coef, double* __restrict__ w, long N)
 {
     const long i = blockIdx.x * (long)kBlk + threadIdx.x;
     if (i >= N) return;
     double s = 0.0;
     for (int c = 0; c < ncols; ++c) s += V[(long)c * ldv + i] * coef[c];
-    w[i] += sign * s;
+    w[i] += s;
 }
 
 __global__ void k_scale(double* __restrict__ y, const double* __restrict__ x, double a, long N)
@@ -227,20 +226,11 @@ ert_status dev_orthogonalise(hipStream_t s, const double* V, long ldv, int ncols
     return ERT_OK;
 }
 
-ert_status dev_gemv_sub(hipStream_t s, const double* V, long ldv, int ncols, const double* coef, double* w,
-                        long N)
-{
-    if (ncols <= 0) return ERT_OK;
-    hipLaunchKernelGGL(k_gemv, dim3(nblocks(N)), dim3(kBlk), 0, s, V, ldv, ncols, coef, w, N, -1.0);
-    ERT_HIP(hipGetLastError());
-    return ERT_OK;
-}
-
 ert_status dev_gemv_add(hipStream_t s, const double* V, long ldv, int ncols, const double* coef, double* x,
                         long N)
 {
     if (ncols <= 0) return ERT_OK;
-    hipLaunchKernelGGL(k_gemv, dim3(nblocks(N)), dim3(kBlk), 0, s, V, ldv, ncols, coef, x, N, 1.0);
+    hipLaunchKernelGGL(k_gemv, dim3(nblocks(N)), dim3(kBlk), 0, s, V, ldv, ncols, coef, x, N);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }

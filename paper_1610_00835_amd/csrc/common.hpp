@@ -426,9 +426,6 @@ void fftpc_destroy(FftPc* f);
 // out[c] = <V[:,c], w> for c < ncols; V has leading dimension ldv.
 ert_status dev_multidot(hipStream_t s, const double* V, long ldv, int ncols, const double* w, long N,
                         double* partial, double* out);
-// w -= V[:, :ncols] * coef   (coef device vector)
-ert_status dev_gemv_sub(hipStream_t s, const double* V, long ldv, int ncols, const double* coef,
-                        double* w, long N);
 // x += V[:, :ncols] * coef   (coef device vector)
 ert_status dev_gemv_add(hipStream_t s, const double* V, long ldv, int ncols, const double* coef,
                         double* x, long N);

@@ -356,13 +356,6 @@ __global__ __launch_bounds__(64 * kLeafWaves) void k_leaf_out(
     io->y[j + (long)b * N] = (op == ERT_OP_A) ? xj - v : v;
 }
 
-template <typename T>
-__global__ void k_zero_t(T* __restrict__ p, long n)
-{
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = T(0);
-}
-
 // --------------------------------------------------- separable transfers ----
 
 // out = contraction of `in` (dims d0 x d1 x d2, x fastest) along `axis` with a
