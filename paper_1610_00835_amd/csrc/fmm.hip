@@ -2464,9 +2464,15 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
         return ERT_OK;
     };
     if (grow(&stage, &stage_elems, st_need) != ERT_OK || grow(&stage_near, &stage_near_elems, sn_need) != ERT_OK) {
-        // FP64 passes work with as few rows as the streaming ones have
+        // FP64 passes work with as few rows as the streaming ones have; what the larger
+        // request got is given back first
         if (!hetero || prec != ERT_FP64 || nrhs <= kPairStreamRhs) return ERT_EDEVICE;
         (void)hipGetLastError();
+        for (T** b : {&stage, &stage_near}) {
+            if (*b) (void)hipFree(*b);
+            *b = nullptr;
+        }
+        stage_elems = stage_near_elems = 0;
         rows_near = rows_far = kPairStreamRhs;
         ERT_TRY(grow(&stage, &stage_elems, rows_far * far_row()));
         ERT_TRY(grow(&stage_near, &stage_near_elems, rows_near * near_row()));
