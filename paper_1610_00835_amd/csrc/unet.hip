@@ -863,6 +863,10 @@ ert_status conv(NetImpl* n, int li, const float* in, long in_b, int in_stride, i
     }
     const dim3 grid(nblocks(a.V, 64), n->B_run);
     const int ct = cout / 16;
+    if (ct < 1 || ct > 8 || ct == 5 || ct == 7) {       // whatever the grid: one rule for every form
+        record_error("net: unsupported channel count");
+        return ERT_EUNSUPPORTED;
+    }
     // tiles of 128 voxels while they fill the chip twice over and two fit a CU's LDS, else of 64
     const int t0 = (a.n0 + 7) / 8, t1 = (a.n1 + 3) / 4;
     const bool big = (long)t0 * t1 * ((a.n2 + 3) / 4) * n->B_run >= 512 && tile_lds(a.cin, a.Kpad, 2) <= 80 * 1024;
@@ -897,8 +901,7 @@ ert_status conv(NetImpl* n, int li, const float* in, long in_b, int in_stride, i
     case 3: ERT_CONV(3) break;
     case 4: ERT_CONV(4) break;
     case 6: ERT_CONV(6) break;
-    case 8: ERT_CONV(8) break;
-    default: record_error("net: unsupported channel count"); return ERT_EUNSUPPORTED;
+    default: ERT_CONV(8) break;
     }
 #undef ERT_CONV
 #undef ERT_CONV_M

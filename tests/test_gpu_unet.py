@@ -366,3 +366,25 @@ def test_coarse_network_fewer_iterations(ev):
     assert plain["converged"] == 1 and m["converged"] == 1 and l["converged"] == 1
     assert l["rel_resid_true"] <= 1e-8 and l["vs_plain"] <= 1e-6
     assert l["iters"] < m["iters"]
+
+
+@pytest.mark.parametrize("n,B", [((8, 8, 8), 1), ((32, 32, 32), 4)])
+@pytest.mark.parametrize("widths,forward", [((80, 16, 16), False), ((16, 112, 16), False), ((32, 64, 128), True)])
+def test_channel_counts_are_refused_at_every_size(ev, n, B, widths, forward):
+    """Output counts of 5, 7 and more than 8 sixteens (80, 112; 192 in the gradient of a
+    concatenation) are unsupported on a small grid as on a large one."""
+    import torch
+    r, e, st, ss = _rand(n, B, 3)
+    with ev.Net(n, batch_max=B, widths=widths) as net:
+        net.set_params(np.zeros(net.size, dtype=np.float32))
+        z = torch.empty((B, int(np.prod(n))), dtype=torch.float64, device="cuda")
+        if forward:
+            net.forward(_dev(r), _dev(st), _dev(ss), z)
+            assert np.array_equal(_host(z), r)          # zero weights: the identity
+        else:
+            with pytest.raises(ev.ErtError) as x:
+                net.forward(_dev(r), _dev(st), _dev(ss), z)
+            assert x.value.status == ev.EUNSUPPORTED
+        with pytest.raises(ev.ErtError) as x:
+            net.grad(_dev(r), _dev(e), _dev(st), _dev(ss))
+        assert x.value.status == ev.EUNSUPPORTED
