@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "up2.hpp"
 
 namespace ertvie {
 namespace {
@@ -590,13 +591,11 @@ __global__ void k_pool2(const float* src, long s_b, int s_stride, int s_off, int
 __global__ void k_up2(const float* src, long s_b, int C, float* dst, long d_b, int d_stride, int d_off, int n0,
                       int n1, int n2)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, C4 = C / 4;
+    const Up2Cell q = up2_cell(blockIdx.x, blockDim.x, threadIdx.x, C, n0, n1);
     const int b = blockIdx.y;
-    const int v = i / C4, c = 4 * (i - v * C4);
-    const int r = v / n0, x = v - r * n0, y = r % n1, z = r / n1;
-    if (z >= n2) return;
-    const long p = x / 2 + (long)(n0 / 2) * (y / 2 + (long)(n1 / 2) * (z / 2));
-    *(v4f*)(dst + (long)b * d_b + (long)v * d_stride + d_off + c) = *(const v4f*)(src + (long)b * s_b + p * C + c);
+    if (q.z >= (unsigned)n2) return;
+    const long p = q.x / 2 + (long)(n0 / 2) * (q.y / 2 + (long)(n1 / 2) * (q.z / 2));
+    *(v4f*)(dst + (long)b * d_b + (long)q.v * d_stride + d_off + q.c) = *(const v4f*)(src + (long)b * s_b + p * C + q.c);
 }
 
 // dst (coarse) = (sum over the 8 children of g channels [g_off, g_off + C)) * (mask > 0)
