@@ -395,7 +395,12 @@ typedef struct {
  *   enable = 1: clear the totals and start recording; 0: stop recording.
  *   stage_ms / stage_launches (host, ERT_NSTAGES entries each, may be NULL):
  *   receive the totals recorded so far (synchronises the stream).
- * Recording adds an event pair per launch; leave it off for timed runs. */
+ * Recording adds an event pair per stage or launch; leave it off for timed runs.  Passes that
+ * run in one kernel are booked under one stage: on one-level homogeneous trees GATHER has
+ * the weights and P2M, NEAR both products, ASSEMBLE their sums, L2P and the assembly; on
+ * FP64 2D homogeneous plans with 8-cell leaves P2M has the weights and L2P the assembly
+ * (GATHER and ASSEMBLE stay zero).  The latter run in fewer launches while nothing is
+ * recorded (the same results; the stages' sum is then more than an apply's time). */
 ERT_API ert_status ert_vie_profile(ert_vie_plan_t plan, int enable, double* stage_ms, int* stage_launches);
 
 /* Build (if needed) the FMM of precision `prec` and describe it (host struct). */

@@ -2629,22 +2629,39 @@ ert_status FmmImpl<T>::enqueue_2d(ert_plan_impl* p, hipStream_t s, int nrhs)
         pr.near = near2d;
         pr.far_offs = m2l_offs;
         pr.near_offs = near_offs;
+        // while stages are timed every stage has launches of its own: the leaves alone, one
+        // level at a time, near field and translations apart
+        Profiler* pf = &p->prof;
+        const int top = pf->on ? tr.L : std::max(2, tr.L - 2), step = pf->on ? 1 : 2;
         {
-            StageTimer st_(&p->prof, s, ERT_STAGE_P2M);
+            StageTimer st_(pf, s, ERT_STAGE_P2M);       // with the weights
             first.kind = 3;
-            first.u = Hom2dUp{cur, io, p->d_ss, t, std::max(2, tr.L - 2), tr.L};
+            first.u = Hom2dUp{cur, io, p->d_ss, t, top, tr.L};
             first.func = hom2d_first_kernel();
             first.grid = hom2d_up_grid(first.u, nrhs);
             first.block = hom2d_up_block(first.u);
             first.shmem = 0;
             ERT_TRY(hom2d_up(s, first.u, nrhs));
         }
-        {
-            StageTimer st_(&p->prof, s, ERT_STAGE_M2L);
-            ERT_TRY(hom2d_products(s, pr, nrhs));
+        if (top > 2) {
+            StageTimer st_(pf, s, ERT_STAGE_M2M);
+            ERT_TRY(hom2d_up_rest(s, first.u, nrhs, step));
         }
-        StageTimer st_(&p->prof, s, ERT_STAGE_L2P);
-        return hom2d_down(s, Hom2dDown{io, p->d_ss, p->d_diag, std::pow(p->geo.h, tr.D), t, 0, 0}, nrhs);
+        if (pf->on) {
+            StageTimer st_(pf, s, ERT_STAGE_NEAR);
+            ERT_TRY(hom2d_products(s, pr, nrhs, true, false));
+        }
+        {
+            StageTimer st_(pf, s, ERT_STAGE_M2L);
+            ERT_TRY(hom2d_products(s, pr, nrhs, !pf->on, true));
+        }
+        const Hom2dDown d{io, p->d_ss, p->d_diag, std::pow(p->geo.h, tr.D), t, 0, 0};
+        if (top > 2) {
+            StageTimer st_(pf, s, ERT_STAGE_L2L);
+            ERT_TRY(hom2d_down(s, d, nrhs, top, step));
+        }
+        StageTimer st_(pf, s, ERT_STAGE_L2P);           // with the assembly
+        return hom2d_out(s, d, nrhs, top);
     }
     return ERT_EINVAL;
 }

@@ -188,14 +188,20 @@ struct Hom2dProducts {
 // (ld x ld each, K used).
 size_t hom2d_fragment_elems(int K);
 ert_status hom2d_fragments(hipStream_t s, const double* src, int ld, int K, long nmat, double* dst);
-// The passes of an apply in their order; `first` is the apply's first launch (top =
-// max(2, L - 2), low = L), with its kernel, grid and block for the root of a captured graph.
+// The passes of an apply in their order: the first launch (top = max(2, L - 2), low = L;
+// kernel, grid and block for the root of a captured graph), the levels above it, the
+// products, the levels down to `last`, and from there to y (last = max(2, L - 2)); `step`
+// levels per launch.  An apply takes two per launch and both products in one; with last = top
+// = L, one level per launch and the products apart its stages are timed one by one, with
+// the same results.
 const void* hom2d_first_kernel();
 dim3 hom2d_up_grid(const Hom2dUp& u, int nrhs);
 dim3 hom2d_up_block(const Hom2dUp& u);
 ert_status hom2d_up(hipStream_t s, const Hom2dUp& first, int nrhs);
-ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs);
-ert_status hom2d_down(hipStream_t s, Hom2dDown d, int nrhs);
+ert_status hom2d_up_rest(hipStream_t s, Hom2dUp first, int nrhs, int step);
+ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs, bool near, bool far);
+ert_status hom2d_down(hipStream_t s, Hom2dDown d, int nrhs, int last, int step);
+ert_status hom2d_out(hipStream_t s, Hom2dDown d, int nrhs, int last);
 
 // Storage of the cached blocks read by the pair products.
 enum {

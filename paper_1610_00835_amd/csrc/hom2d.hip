@@ -351,21 +351,27 @@ dim3 hom2d_up_block(const Hom2dUp& u) { return dim3(64u << (2 * (u.low - u.top))
 ert_status hom2d_up(hipStream_t s, const Hom2dUp& first, int nrhs)
 {
     hipLaunchKernelGGL(k_up<true>, hom2d_up_grid(first, nrhs), hom2d_up_block(first), 0, s, first);
-    for (Hom2dUp u = first; u.top > 2;) {
+    ERT_HIP(hipGetLastError());
+    return ERT_OK;
+}
+
+ert_status hom2d_up_rest(hipStream_t s, Hom2dUp u, int nrhs, int step)
+{
+    while (u.top > 2) {
         u.low = u.top;
-        u.top = std::max(2, u.low - 2);
+        u.top = std::max(2, u.low - step);
         hipLaunchKernelGGL(k_up<false>, hom2d_up_grid(u, nrhs), hom2d_up_block(u), 0, s, u);
     }
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }
 
-ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs)
+ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs, bool near, bool far)
 {
     const Hom2d& t = p.t;
-    p.near_tiles = (t.nl0[t.L] * t.nl1[t.L] + 15) / 16;
+    p.near_tiles = near ? (t.nl0[t.L] * t.nl1[t.L] + 15) / 16 : 0;
     int tiles = p.near_tiles;
-    for (int l = 2; l <= t.L; ++l) tiles += p.tiles[l] = far_tiles(t, l);
+    for (int l = 2; l <= t.L && far; ++l) tiles += p.tiles[l] = far_tiles(t, l);
     switch (t.nc) {
     case 2: launch_products<2>(s, p, tiles, nrhs); break;
     case 3: launch_products<3>(s, p, tiles, nrhs); break;
@@ -380,22 +386,29 @@ ert_status hom2d_products(hipStream_t s, Hom2dProducts p, int nrhs)
     return ERT_OK;
 }
 
-ert_status hom2d_down(hipStream_t s, Hom2dDown d, int nrhs)
+ert_status hom2d_down(hipStream_t s, Hom2dDown d, int nrhs, int last, int step)
 {
     const Hom2d& t = d.t;
-    const int last = std::max(2, t.L - 2);      // the level from which the last launch goes to y
-    auto grid = [&](int top) { return dim3((unsigned)(t.nl0[top] * t.nl1[top]), (unsigned)nrhs); };
-    // the steps above it: two levels each, an odd one first
+    // an odd step first, then `step` levels each
     for (int top = 2; top < last;) {
-        const int low = std::min(last, top + ((last - top) % 2 ? 1 : 2));
+        const int low = std::min(last, top + ((last - top) % step ? 1 : step));
         d.top = top;
         d.low = low;
-        hipLaunchKernelGGL(k_down<false>, grid(top), dim3(64u << (2 * (low - top))), 0, s, d);
+        hipLaunchKernelGGL(k_down<false>, dim3((unsigned)(t.nl0[top] * t.nl1[top]), (unsigned)nrhs),
+                           dim3(64u << (2 * (low - top))), 0, s, d);
         top = low;
     }
+    ERT_HIP(hipGetLastError());
+    return ERT_OK;
+}
+
+ert_status hom2d_out(hipStream_t s, Hom2dDown d, int nrhs, int last)
+{
+    const Hom2d& t = d.t;
     d.top = last;
     d.low = t.L;
-    hipLaunchKernelGGL(k_down<true>, grid(last), dim3(64u << (2 * (t.L - last))), 0, s, d);
+    hipLaunchKernelGGL(k_down<true>, dim3((unsigned)(t.nl0[last] * t.nl1[last]), (unsigned)nrhs),
+                       dim3(64u << (2 * (t.L - last))), 0, s, d);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }

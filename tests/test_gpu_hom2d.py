@@ -44,3 +44,23 @@ def test_hom2d_equals_general_passes(n, order, scheme):
     with ertvie.Plan(2, n, h, np.full(N, 3.0), ss, form=(1, 1), svd_tol=-1.0, **kw) as a, \
             ertvie.Plan(2, n, h, np.full(N, 3.0), ss, svd_tol=-1.0, **kw) as b:
         assert rel_l2(gpu_apply(b, X[:, 1], ertvie.OP_GS), gpu_apply(a, X[:, 1], ertvie.OP_GS)) <= 1e-12
+
+
+@pytest.mark.parametrize("n", [(24, 24), (39, 70), (264, 264)])
+def test_stage_profile(n):
+    """Every stage that the plan has is timed: near field, P2M, translations and L2P on any tree,
+    M2M and L2L above a second far level; the results stay those of an unprofiled apply."""
+    from paper_1610_00835_amd import ertvie
+    N = n[0] * n[1]
+    x = inputs.random_vector(N, 3)
+    with ertvie.Plan(2, n, 1.0 / max(n), np.full(N, 3.0), np.full(N, 2.0), method="fmm", cheb_n=6) as plan:
+        levels = plan.fmm_info()["levels"]
+        want = gpu_apply(plan, x, ertvie.OP_A)
+        plan.profile(True)
+        got = gpu_apply(plan, x, ertvie.OP_A)
+        prof = plan.profile(False)
+        assert np.array_equal(got, want)
+        for _ in range(3):
+            assert np.array_equal(gpu_apply(plan, x, ertvie.OP_A), want)
+    stages = {"near", "p2m", "m2l", "l2p"} | ({"m2m", "l2l"} if levels > 2 else set())
+    assert {k for k, v in prof.items() if v[0] > 0.0 and v[1] > 0} == stages
