@@ -66,9 +66,57 @@ __device__ __forceinline__ double phi1_one(const Phi1& f, double x)
 // exp(-x) - 1; a call, so that its constants don't sit in registers through the march
 __device__ __noinline__ double thick_step(double x) { return expm1(-x); }
 
+// Steps of the ray from cell c backwards along -v to the box boundary, and their length.
+template <int DIM>
+__device__ __forceinline__ void ray_steps(double h, const int (&n)[3], const int (&c)[DIM], const double (&v)[DIM], int* m,
+                                          double* D)
+{
+    double sb = 1e300;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const double x = h * (c[a] + 0.5);
+        if (v[a] > 0.0) sb = fmin(sb, x / v[a]);
+        else if (v[a] < 0.0) sb = fmin(sb, (n[a] * h - x) / (-v[a]));
+    }
+    // the relative margin keeps the count of an exact multiple of h/2 (every
+    // axis-parallel ray) independent of the last bit of sb
+    const double q0 = ceil(sb / (0.5 * h) * (1.0 - 1e-12));
+    *m = q0 < 1.0 ? 1 : (int)q0;
+    *D = sb / (double)*m;
+}
+
+// One step of length D in (sigma_t, Q) = s: att = exp(-tau) before the step.
+__device__ __forceinline__ void ray_step(const Phi1& coef, double2 s, double D, double& acc, double& att)
+{
+    const double sd = s.x * D;
+    double step, em;         // integral of exp over the step, exp(-sigma D) - 1
+    if (!__ballot(!(sd >= 0.0 && sd <= 0.25))) {
+        const double p = phi1_quarter(coef, sd);
+        step = D * p;
+        em = -sd * p;
+    } else if (!__ballot(!(sd >= 0.0 && sd <= 1.0))) {
+        const double p = phi1_one(coef, sd);
+        step = D * p;
+        em = -sd * p;
+    } else {
+        em = thick_step(sd);
+        step = sd > 1e-300 ? -em / s.x : D;
+    }
+    acc = fma(att * s.y, step, acc);
+    att = fma(att, em, att);
+}
+
 // A workgroup's cells, 2^s per axis: 8 x 8 x 8 in 3D and 32 x 16 in 2D; grids thinner than that
-// give the rest to their longer axes.  Compact tiles keep the rays of a wave near each other in
-// length (64 cells of a row: a third of the steps were idle).
+// give the rest to their longer axes (4 x 128 at most: no side is below kThin + 1).  Compact
+// tiles keep the rays of a wave near each other in length (64 cells of a row: a third of the
+// steps were idle).
+//
+// Grids whose shortest side is at most kThin cells take one ray per thread with its samples from
+// memory (k_sweep_thin): their rays have a few steps, and staging and its barriers cost more
+// than the gathers.  Staged and gathered: 1 x 1 x 4096, 8 directions, 31 and 26 us a call; 2 x 300 x
+// 300, 4 directions, 89 and 83; 3 x 300 x 300 129 and 116; 4 x 300 x 300 148 and 163; 2D 2 x 4096
+// 31 and 29, 4 x 4096 37 and 38.
+constexpr int kThin = 3;
 constexpr int kSweepThreads = 512;
 constexpr double kSlack = 1e-6;        // cells
 constexpr int kSweepCells = 3328;      // staged box, (sigma_t, Q) pairs: three workgroups per CU
@@ -84,7 +132,7 @@ SweepTile sweep_tile(const Geo& g)
             --t.s[a];
             int best = -1;
             for (int b = 0; b < g.dim; ++b)
-                if (b != a && t.s[b] < 6 && (1 << t.s[b]) < n[b] && (best < 0 || n[b] >> t.s[b] > n[best] >> t.s[best])) best = b;
+                if (b != a && (1 << t.s[b]) < n[b] && (best < 0 || n[b] >> t.s[b] > n[best] >> t.s[best])) best = b;
             if (best >= 0) ++t.s[best];
         }
     return t;
@@ -94,10 +142,11 @@ SweepTile sweep_tile(const Geo& g)
 // between distances w W and (w + 1) W (in cells) are a box, staged in LDS before the window, cells
 // outside the grid with the value of the face (the clamped rule).  In cells the sample q = 1/2,
 // 3/2, .. of cell i sits at i - q e per axis (cell centres are whole numbers); the box allows it
-// a rounding of kSlack.  W is the largest whose box fits for this direction, 16 cells at most.
+// a rounding of kSlack.  W is the largest whose box fits for this direction, at most 16 cells and
+// the longest ray of the tile.
 // Bound: FP64 arithmetic (75 instructions per step; a hundred and fifty with clamps, expm1 and a
 // division), then LDS reads (eight corners of 16 bytes; as gathers through L1 at half the rate
-// they were the bound).  64^3 x 26 directions: 2.4 -> 1.6 ms; 512^2 x 26: 12.5 -> 5.8 ms.
+// they were the bound).  64^3 x 26 directions: 2.46 -> 1.52 ms; 512^2 x 26: 12.5 -> 5.8 ms.
 template <int DIM>
 __global__ __launch_bounds__(kSweepThreads, 6) void k_sweep(Geo g, SweepTile tile, Phi1 coef,
                                                             const double2* __restrict__ sq,
@@ -125,25 +174,21 @@ __global__ __launch_bounds__(kSweepThreads, 6) void k_sweep(Geo g, SweepTile til
         }
         in = in && t == 0;
     }
-    // distance backwards along -v to the box boundary
-    double sb = 1e300;
+    int m;
+    double D;
+    ray_steps<DIM>(h, n, c, v, &m, &D);
+    if (!in) m = 0, D = h;
+    const double per_cell = h / D;   // steps per cell length
+    double e[DIM], longest = 16.0;   // longest: no ray of the tile is longer (cells)
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        const double x = h * (c[a] + 0.5);
-        if (v[a] > 0.0) sb = fmin(sb, x / v[a]);
-        else if (v[a] < 0.0) sb = fmin(sb, (n[a] * h - x) / (-v[a]));
+        const int last = lo[a] + (1 << tile.s[a]) - 1, top = last < n[a] - 1 ? last : n[a] - 1;
+        if (v[a] > 0.0) longest = fmin(longest, (top + 0.5) / v[a]);
+        else if (v[a] < 0.0) longest = fmin(longest, (n[a] - lo[a] - 0.5) / -v[a]);
+        e[a] = -D * v[a] / h;
     }
-    // the relative margin keeps the count of an exact multiple of h/2 (every
-    // axis-parallel ray) independent of the last bit of sb
-    const double q0 = ceil(sb / (0.5 * h) * (1.0 - 1e-12));
-    const int m = !in ? 0 : q0 < 1.0 ? 1 : (int)q0;
-    const double D = in ? sb / (double)m : h;
-    const double per_cell = h / D;   // steps per cell length
-    double e[DIM];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) e[a] = -D * v[a] / h;
     // the window
-    int W = 16;
+    int W = (int)ceil(longest);
     for (; W > 1; --W) {
         int vol = 1;
 #pragma unroll
@@ -210,27 +255,68 @@ __global__ __launch_bounds__(kSweepThreads, 6) void k_sweep(Geo g, SweepTile til
                 const double2 y = plane(b + o2);
                 s = make_double2(fma(t[DIM - 1], y.x - s.x, s.x), fma(t[DIM - 1], y.y - s.y, s.y));
             }
-            const double sd = s.x * D;
-            double step, em;         // integral of exp over the step, exp(-sigma D) - 1
-            if (!__ballot(!(sd >= 0.0 && sd <= 0.25))) {
-                const double p = phi1_quarter(coef, sd);
-                step = D * p;
-                em = -sd * p;
-            } else if (!__ballot(!(sd >= 0.0 && sd <= 1.0))) {
-                const double p = phi1_one(coef, sd);
-                step = D * p;
-                em = -sd * p;
-            } else {
-                em = thick_step(sd);
-                step = sd > 1e-300 ? -em / s.x : D;
-            }
-            acc = fma(att * s.y, step, acc);
-            att = fma(att, em, att);
+            ray_step(coef, s, D, acc, att);
         }
     }
     if (!in) return;
     long j = c[0] + (long)n[0] * c[1];
     if constexpr (DIM > 2) j += (long)n[0] * n[1] * c[DIM - 1];
+    phi[(long)d * N + j] = acc;
+}
+
+// One ray per thread with its samples from memory: grids of at most kThin cells on some axis.
+template <int DIM>
+__global__ __launch_bounds__(256) void k_sweep_thin(Geo g, Phi1 coef, const double2* __restrict__ sq,
+                                                    const double* __restrict__ dirs, long N, double* __restrict__ phi)
+{
+    const long j = blockIdx.x * 256L + threadIdx.x;
+    if (j >= N) return;
+    const int d = blockIdx.y;
+    const double h = g.h;
+    const int n[3] = {g.n0, g.n1, DIM > 2 ? g.n2 : 1};
+    int c[DIM];
+    double v[DIM], e[DIM];
+    long rest = j;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        c[a] = (int)(rest % n[a]);
+        rest /= n[a];
+        v[a] = dirs[DIM * d + a];
+    }
+    int m;
+    double D;
+    ray_steps<DIM>(h, n, c, v, &m, &D);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) e[a] = -D * v[a] / h;
+    double acc = 0.0, att = 1.0, q = 0.5;
+    for (int k = 0; k < m; ++k, q += 1.0) {
+        double t[DIM];
+        long at[DIM][2];
+        long stride = 1;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            const double u = fma(q, e[a], (double)c[a]), f = floor(u);
+            const int i = (int)f;
+            t[a] = u - f;
+            at[a][0] = stride * min(max(i, 0), n[a] - 1);
+            at[a][1] = stride * min(max(i + 1, 0), n[a] - 1);
+            stride *= n[a];
+        }
+        auto line = [&](long o) {
+            const double2 x = sq[at[0][0] + o], y = sq[at[0][1] + o];
+            return make_double2(fma(t[0], y.x - x.x, x.x), fma(t[0], y.y - x.y, x.y));
+        };
+        auto plane = [&](long o) {
+            const double2 x = line(at[1][0] + o), y = line(at[1][1] + o);
+            return make_double2(fma(t[1], y.x - x.x, x.x), fma(t[1], y.y - x.y, x.y));
+        };
+        double2 s = plane(DIM > 2 ? at[DIM - 1][0] : 0);
+        if constexpr (DIM > 2) {
+            const double2 y = plane(at[DIM - 1][1]);
+            s = make_double2(fma(t[DIM - 1], y.x - s.x, s.x), fma(t[DIM - 1], y.y - s.y, s.y));
+        }
+        ray_step(coef, s, D, acc, att);
+    }
     phi[(long)d * N + j] = acc;
 }
 
@@ -272,14 +358,19 @@ ert_status sweep_into(ert_plan_impl* p, const double* U, const double* f, const 
     }
     const SweepTile tile = sweep_tile(p->geo);
     const int n[3] = {p->geo.n0, p->geo.n1, dim > 2 ? p->geo.n2 : 1};
+    const bool thin = std::min(std::min(n[0], n[1]), dim > 2 ? n[2] : n[1]) <= kThin;
     long tiles = 1;
     for (int a = 0; a < dim; ++a) tiles *= (n[a] + (1 << tile.s[a]) - 1) >> tile.s[a];
     // directions in slabs of at most 65535 (grid.y)
     for (int d0 = 0; d0 < ndir && st == ERT_OK; d0 += 65535) {
         const int nd = std::min(65535, ndir - d0);
-        hipLaunchKernelGGL((dim == 2 ? k_sweep<2> : k_sweep<3>), dim3((unsigned)tiles, (unsigned)nd),
-                           dim3(kSweepThreads), 0, p->stream, p->geo, tile, kPhi1, sq, dd + (size_t)dim * d0, N,
-                           phi + (size_t)d0 * N);
+        if (thin)
+            hipLaunchKernelGGL((dim == 2 ? k_sweep_thin<2> : k_sweep_thin<3>), dim3((unsigned)((N + 255) / 256), (unsigned)nd),
+                               dim3(256), 0, p->stream, p->geo, kPhi1, sq, dd + (size_t)dim * d0, N, phi + (size_t)d0 * N);
+        else
+            hipLaunchKernelGGL((dim == 2 ? k_sweep<2> : k_sweep<3>), dim3((unsigned)tiles, (unsigned)nd),
+                               dim3(kSweepThreads), 0, p->stream, p->geo, tile, kPhi1, sq, dd + (size_t)dim * d0, N,
+                               phi + (size_t)d0 * N);
         st = ERT_HIPST(hipGetLastError());
     }
     const ert_status ss = ERT_HIPST(hipStreamSynchronize(p->stream));

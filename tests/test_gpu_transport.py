@@ -90,3 +90,19 @@ def test_transport_tiles_and_step_ranges(ev, n, scale):
     got = _run(ev, case, U, case["f"], dirs)
     ref = T.recover(U, case["f"], st, 0.9 * st, n, h, dirs)
     assert max(rel_l2(got[k], ref[:, k]) for k in range(len(dirs))) <= 1e-12
+
+
+@pytest.mark.parametrize("n", [(1, 1, 600), (2, 2, 300), (600, 1, 1), (1, 700, 1), (3, 2, 129), (2, 260, 1), (1, 30, 80),
+                               (1, 600), (700, 1), (2, 300), (150, 3), (2, 70, 90)])
+def test_transport_thin_grids(ev, n):
+    """Tiles up to a line of 512 cells and short rays (small windows), axis-parallel directions
+    among them; independent cell values."""
+    N, h, d = int(np.prod(n)), 0.1, len(n)
+    rng = np.random.default_rng(N)
+    st = rng.uniform(0.5, 8.0, N)
+    case = {"dim": d, "n": n, "h": h, "kernel": 1, "sigma_t": st, "sigma_s": 0.9 * st, "f": rng.uniform(0, 1, N)}
+    U = rng.uniform(0, 1, N)
+    dirs = np.concatenate([_dirs(d, 5, 4), np.eye(d), -np.eye(d)])
+    got = _run(ev, case, U, case["f"], dirs)
+    ref = T.recover(U, case["f"], st, 0.9 * st, n, h, dirs)
+    assert max(rel_l2(got[k], ref[:, k]) for k in range(len(dirs))) <= 1e-12
