@@ -61,6 +61,9 @@ constexpr int kMaxPeriod = 1024;
 // Lines per workgroup: 16 (whole lines of memory across the axis), fewer while a workgroup
 // takes more than a fifth of a CU's LDS or there are fewer than two workgroups per CU.
 // 96^3 (periods of 192): 16 lines in 60 KB 152 us, 8 lines 111 us; 100 x 264: 31 and 23 us.
+// Across the axis four lines (32 contiguous bytes) are kept up to the whole 64 KB while they
+// give two workgroups per CU: 192^3 872 us with two lines, 670 with four; 256^3 2180 and 1583.
+// 264^2 has too few: four lines 36 us, one 29.
 constexpr size_t kLdsWant = 32 * 1024;
 constexpr long kMinGroups = 512;
 
@@ -184,6 +187,10 @@ __device__ __forceinline__ void dft(Cx<R> (&x)[RAD], const Cx<R>* __restrict__ t
 // stores, eight elements apart from thread to thread, spread over the banks.
 __host__ __device__ __forceinline__ int slot(int i) { return i + (i >> 3); }
 
+// LDS pitch of a position: lines that run along the contiguous axis are moved by position
+// first, lines across it by line.
+__host__ __device__ __forceinline__ int line_pitch(int TX, bool along) { return TX > 1 && along ? TX + 1 : TX; }
+
 template <typename R, int RAD>
 __device__ void fft_stage(const Cx<R>* __restrict__ in, Cx<R>* __restrict__ out, const Cx<R>* __restrict__ tw,
                           int m, int p, int LTX, int TXP, bool inv)
@@ -242,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void k_lines(Lines L, const void* src_, v
                                                     const Cx<R>* __restrict__ tw)
 {
     extern __shared__ unsigned char lds_raw[];
-    const int m = L.m, LTX = L.LTX, TX = 1 << LTX, TXP = TX == 1 ? 1 : TX + 1;
+    const int m = L.m, LTX = L.LTX, TX = 1 << LTX, TXP = line_pitch(TX, L.si == 1 || L.di == 1);
     Cx<R>* tws = reinterpret_cast<Cx<R>*>(lds_raw);
     Cx<R>* b0 = tws + m;
     Cx<R>* b1 = b0 + (size_t)slot(m) * TXP;
@@ -423,19 +430,21 @@ __global__ __launch_bounds__(kThreads) void k_symbol(const Cx<double>* __restric
 }
 
 template <typename R>
-size_t lds_bytes(int m, int TX)
+size_t lds_bytes(int m, int TX, bool along)
 {
-    const int TXP = TX == 1 ? 1 : TX + 1;
-    return sizeof(Cx<R>) * ((size_t)m + 2 * (size_t)slot(m) * TXP);
+    return sizeof(Cx<R>) * ((size_t)m + 2 * (size_t)slot(m) * line_pitch(TX, along));
 }
 
 template <typename R, int MODE, bool INV>
 ert_status launch_lines(hipStream_t s, Lines L, const void* src, void* dst, const Cx<R>* tw)
 {
+    const bool along = L.si == 1 || L.di == 1;
+    auto groups = [&](int ltx) { return (long)((L.A + (1 << ltx) - 1) >> ltx) * L.B; };
     L.LTX = 4;
-    while (L.LTX > 0 && lds_bytes<R>(L.m, 1 << L.LTX) > kLdsWant) --L.LTX;
-    while (L.LTX > (L.si == 1 || L.di == 1 ? 0 : 2) && (long)((L.A + (1 << L.LTX) - 1) >> L.LTX) * L.B < kMinGroups) --L.LTX;
-    const size_t lds = lds_bytes<R>(L.m, 1 << L.LTX);
+    while (L.LTX > 0 && lds_bytes<R>(L.m, 1 << L.LTX, along) >
+                            (!along && L.LTX == 2 && groups(2) >= kMinGroups ? kLdsMax : kLdsWant)) --L.LTX;
+    while (L.LTX > 0 && groups(L.LTX) < kMinGroups) --L.LTX;
+    const size_t lds = lds_bytes<R>(L.m, 1 << L.LTX, along);
     if (lds > kLdsMax) {
         record_error("ert_vie_fft_precond: line transform does not fit in LDS");
         return ERT_EUNSUPPORTED;

@@ -183,3 +183,21 @@ def test_fft_with_network_and_judge(ev):
     assert rel_l2(Ug, U0) <= 1e-6
     assert bad["converged"] == 1 and bad["rejected"] >= 1 and np.all(np.isfinite(Ub))
     assert rel_l2(Ub, U0) <= 1e-6
+
+
+# long periods on every axis: 384 and 500 across the axis with four lines per workgroup, 800 with
+# the most LDS they take, 1024 with one, 600 along it; few workgroups (2D) with one
+@pytest.mark.parametrize("n", [(60, 60, 192), (60, 250, 30), (40, 30, 400), (20, 512, 20), (300, 40, 33), (264, 264),
+                               (20, 30, 112)])
+def test_long_periods_match_reference(ev, n):
+    case = _case(len(n), n, 3, "rough")
+    N = int(np.prod(n))
+    r = np.random.default_rng(4).standard_normal((N, 2))
+    with ev.plan_from_case(case, nrhs_max=2) as plan:
+        assert plan.fft_info()["m"][:len(n)] == list(F.periods(n))
+        z = to_host(plan.fft_precond(to_dev(r), to_dev(np.zeros((N, 2)))))
+    for k in range(2):
+        zo = F.apply(r[:, k], len(n), n, case["h"], case["sigma_t"], case["sigma_s"])
+        err = rel_l2(z[:, k], zo)
+        log("fft preconditioner", n, "rel L2", err)
+        assert err <= BAR
