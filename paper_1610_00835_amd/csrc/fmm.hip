@@ -1582,12 +1582,17 @@ struct FmmImpl : FmmData {
     T* stage = nullptr;                 // staging rows of the far-field products
     T* stage_near = nullptr;            // staging rows of the near-field products (runs concurrently)
     size_t stage_near_elems = 0;
-    size_t rows_near = 0, rows_far = 0; // heterogeneous: staging rows of a pass that the buffers hold
-    size_t near_row() const { return (size_t)tr.nleaf * (tr.D == 3 ? 27 : 9) * tr.S; }
-    size_t far_row() const
+    // heterogeneous: elements that `rows` staging rows take (rows <= 0: those of a pass of nrhs)
+    size_t near_stage(int rows, int nrhs) const
+    {
+        if (rows <= 0) rows = pair_rows(prec == ERT_FP64 ? ERT_FP64 : ERT_FP32, tr.S, nrhs, hc->near_np);
+        return (size_t)rows * tr.nleaf * (tr.D == 3 ? 27 : 9) * tr.S;
+    }
+    size_t far_stage(int rows, int nrhs) const
     {
         size_t n = 0;
-        for (int l = 2; l <= tr.L; ++l) n = std::max(n, (size_t)hc->hnd[l] * tr.Kp);
+        for (int l = 2; l <= tr.L; ++l)
+            n = std::max(n, (size_t)(rows > 0 ? rows : pair_rows(prec, tr.Kp, nrhs, hc->hnp[l])) * hc->hnd[l] * tr.Kp);
         return n;
     }
     // the near field and the far-field passes are independent until L2P: after the
@@ -2447,10 +2452,8 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
     ERT_TRY(site_need(near_site, tr.nleaf, tr.S, sn_need));
     if (hetero) {
         // staging rows (one per directed pair) of a pass of the products
-        rows_near = pair_rows(prec == ERT_FP64 ? ERT_FP64 : ERT_FP32, tr.S, nrhs);
-        rows_far = pair_rows(prec, tr.Kp, nrhs);
-        sn_need = std::max(sn_need, rows_near * near_row());
-        st_need = std::max(st_need, rows_far * far_row());
+        sn_need = std::max(sn_need, near_stage(0, nrhs));
+        st_need = std::max(st_need, far_stage(0, nrhs));
     }
     for (int l = 2; l <= tr.L; ++l)
         ERT_TRY(site_need(far_site[l], tr.nbox[l], rp[l] > 0 ? rp[l] : tr.Kp, st_need));
@@ -2473,9 +2476,8 @@ ert_status FmmImpl<T>::ensure_buffers(int nrhs)
             *b = nullptr;
         }
         stage_elems = stage_near_elems = 0;
-        rows_near = rows_far = kPairStreamRhs;
-        ERT_TRY(grow(&stage, &stage_elems, rows_far * far_row()));
-        ERT_TRY(grow(&stage_near, &stage_near_elems, rows_near * near_row()));
+        ERT_TRY(grow(&stage, &stage_elems, far_stage(kPairStreamRhs, nrhs)));
+        ERT_TRY(grow(&stage_near, &stage_near_elems, near_stage(kPairStreamRhs, nrhs)));
     }
     if (tu_need > tune_elems) {
         if (tune) (void)hipFree(tune);
@@ -2728,7 +2730,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
             a.nsrc = tr.nleaf;
             a.W = q;
             a.stage = stage_near;
-            a.rows = rows_near;
+            a.rows = stage_near_elems / ((size_t)a.nrows * a.M);
             a.L = pot;
             a.accumulate = 0;
             st_.pause();
@@ -2815,7 +2817,7 @@ ert_status FmmImpl<T>::enqueue(ert_plan_impl* p, hipStream_t s, int nrhs)
                 a.nsrc = tr.nbox[l];
                 a.W = W[l];
                 a.stage = stage;
-                a.rows = rows_far;
+                a.rows = a.nrows > 0 ? stage_elems / ((size_t)a.nrows * a.M) : 0;
                 a.L = Lc[l];
                 a.accumulate = first ? 0 : 1;
                 st_.pause();

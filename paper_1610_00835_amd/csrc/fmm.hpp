@@ -239,7 +239,7 @@ struct PairStream {
     long nsrc;               // boxes (W is [B][nsrc][M])
     const void* W;
     void* stage;             // [rows][nrows][M]
-    size_t rows;             // right-hand sides it holds: pair_rows(), or (FP64) at least kPairStreamRhs
+    size_t rows;             // right-hand sides it holds: at least pair_rows(), or (FP64) kPairStreamRhs
     void* L;                 // [B][ntarget][M]
     int accumulate;
     int used;                // rows and columns of a block past these are zero (padding; M: none)
@@ -258,21 +258,41 @@ constexpr int kPairDualMinRhs = 3;
 // Right-hand sides of a pass: streaming form, FP64 and FP32 matrix-core forms.
 constexpr int kPairStreamRhs = 4, kPairDualRhs = 32, kPairMfmaRhs = 64;
 
-// FP64, `left` right-hand sides still to do: whether the next pass takes 64 in two
-// launches, 7 % faster than two passes of 32 (48^3, order 6: 6.5 against 6.9 ms) where 64
-// columns are nearly full and the blocks give its 256-row tiles enough to do; 2D blocks
-// of 64 rows take 0.64 ms instead of 1.24 in passes of 32.
-inline bool pair_pass64(int M, int left) { return left > 48 && M > 128; }
+constexpr long kPairCus = 256;            // compute units of the chip
 
-// Staging rows (right-hand sides of one pass) of the products of M x M blocks for nrhs
-// right-hand sides.
-inline int pair_rows(int prec, int M, int nrhs)
+// FP64, `left` right-hand sides still to do for np blocks: whether the next pass takes 64 in
+// two launches.  Where 64 columns are nearly full and the blocks give its 256-row tiles
+// enough to do that is 7 % faster than two passes of 32 (48^3, order 6: 6.5 against 6.9 ms; 2D
+// blocks of 64 rows: 1.24 against 0.64).  Of the larger blocks from 33 on also where the two
+// tiles of each leave no CU a second one: two launches of one round then stand against passes
+// of 32 and 16 (16^3, 36 blocks of 512 rows, 40 columns: 229 against 288 us; 24^3, 185
+// blocks: 446 against 337).
+inline bool pair_pass64(int M, int left, long np)
 {
-    const bool pieces = M % 4 == 0;      // matrix-core forms take whole 4-value pieces
+    return M > 128 && (left > 48 || (left > 32 && M > 256 && 2 * np <= kPairCus));
+}
+
+// FP64 on the matrix cores (16, 32 or 64 columns per pass).  Blocks of more than 384 rows run
+// one workgroup per CU, in rounds of 90 to 98 us whatever the columns up to 16; three and four
+// columns are streamed, in two passes of 48 + 0.41 np us but 115 at least, where the last
+// round would be mostly idle (32^3, 532 blocks in 3 rounds: 292 against 265 us; 24^3, 185 in
+// one: 98 against 115; 40^3, 1161 in 5: 489 against 484).
+inline bool pair_on_matrix_cores(int M, int nrhs, long np)
+{
+    if (M % 4 != 0 || nrhs < kPairDualMinRhs) return false;       // whole 4-value pieces
+    if (M <= 384 || nrhs > kPairStreamRhs) return true;
+    const double streamed = 48.0 + 0.41 * np;
+    return 94.0 * ((np + kPairCus - 1) / kPairCus) <= (streamed > 115.0 ? streamed : 115.0);
+}
+
+// Staging rows (right-hand sides of one pass) of the products of np M x M blocks for nrhs
+// right-hand sides.
+inline int pair_rows(int prec, int M, int nrhs, long np)
+{
     int rows = kPairStreamRhs;
     if (prec == ERT_BF16X3) rows = kPairMfmaRhs;
-    else if (prec == ERT_FP64 && pieces && nrhs >= kPairDualMinRhs) rows = pair_pass64(M, nrhs) ? kPairMfmaRhs : kPairDualRhs;
-    else if (prec == ERT_FP32 && pieces && nrhs >= kPairMfmaMinRhs) rows = kPairMfmaRhs;
+    else if (prec == ERT_FP64 && pair_on_matrix_cores(M, nrhs, np)) rows = pair_pass64(M, nrhs, np) ? kPairMfmaRhs : kPairDualRhs;
+    else if (prec == ERT_FP32 && M % 4 == 0 && nrhs >= kPairMfmaMinRhs) rows = kPairMfmaRhs;
     return nrhs < rows ? nrhs : rows;
 }
 

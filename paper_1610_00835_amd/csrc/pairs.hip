@@ -1086,8 +1086,10 @@ ert_status pair_dual_t(hipStream_t s, const PairStream& g, const PairGen* gen)
     }
     const int rblocks = (g.M + 64 * RTB - 1) / (64 * RTB);
     for (int b0 = 0, nb = 0; b0 < g.B; b0 += nb) {
-        const bool wide = pair_pass64(g.M, std::min<int>(g.B - b0, (int)g.rows));
-        nb = std::min(std::min(wide ? kPairMfmaRhs : kPairDualRhs, (int)g.rows), g.B - b0);
+        const int left = g.B - b0;
+        // (a pass of 64 writes all of them)
+        const bool wide = g.rows >= (size_t)std::min(left, kPairMfmaRhs) && pair_pass64(g.M, left, g.npairs);
+        nb = (int)std::min<size_t>(std::min(wide ? kPairMfmaRhs : kPairDualRhs, left), g.rows);
         {
             StageTimer t_(g.prof, s, g.prof_stage);
             ERT_TRY(for_each_chunk(s, g, gen, [&](const PairStream& c) -> ert_status {
@@ -1158,7 +1160,7 @@ ert_status pair_stream(hipStream_t s, int prec, const PairStream& g, const PairG
         }
         return pair_mfma_bf16x3(s, g, gen);
     }
-    if (f64 && g.B >= kPairDualMinRhs && g.M % 4 == 0)
+    if (f64 && pair_on_matrix_cores(g.M, g.B, g.npairs))
         return g.ops_fmt == kOpsSplit ? pair_dual_t<OpsSplit>(s, g, gen) : pair_dual_t<float>(s, g, gen);
     if (!f64 && g.B >= kPairMfmaMinRhs && g.M % 4 == 0) {
         switch (g.ops_fmt) {

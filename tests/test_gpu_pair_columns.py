@@ -29,3 +29,19 @@ def test_columns_equal_single_applies(n, leaf, order):
         for nrhs in (2, 3, 4, 5, 16, 17, 32, 33, 48, 49, 64, 67):
             Y = gpu_apply(plan, np.asfortranarray(X[:, :nrhs]), ertvie.OP_A)
             assert max(rel_l2(Y[:, b], one[:, b]) for b in range(nrhs)) <= 1e-12, nrhs
+
+
+# few blocks, where 33 columns and more take one pass of 64, and blocks of 512 rows whose rounds of
+# workgroups end nearly empty, where 3 and 4 columns are streamed (64 leaves: 532 pairs)
+@pytest.mark.parametrize("n,order", [((16, 16, 16), 6), ((20, 17, 24), 6), ((32, 32, 32), 4)])
+def test_columns_of_few_blocks(n, order):
+    from paper_1610_00835_amd import ertvie
+    case = inputs.make_case("c3", n=n, seed=2)
+    case["h"] = 1.0 / 32
+    N = int(np.prod(n))
+    X = inputs.random_vector(N, 5, nrhs=100)
+    with ertvie.plan_from_case(case, method="fmm", prec="fp64", cheb_n=order, nrhs_max=100) as plan:
+        one = np.stack([gpu_apply(plan, np.ascontiguousarray(X[:, b]), ertvie.OP_A) for b in range(100)], axis=1)
+        for nrhs in (3, 4, 5, 33, 48, 49, 100, 36):
+            Y = gpu_apply(plan, np.asfortranarray(X[:, :nrhs]), ertvie.OP_A)
+            assert max(rel_l2(Y[:, b], one[:, b]) for b in range(nrhs)) <= 1e-12, nrhs
