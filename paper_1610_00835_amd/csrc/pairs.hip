@@ -882,10 +882,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 }
 
 // Per-target sums of the staging rows (rhs b0..b0+nb-1), over the target's
-// contiguous directed rows in order, skipping rows of pairs that do not exist.
+// contiguous directed rows in order, skipping rows of pairs that do not exist (ROWS: marked
+// in row_src; near fields of thin grids have as few as 3 of 27).
 // Bound: the staging rows' traffic; eight rows are in flight per thread (one at a time,
 // behind its index: 48^3, order 6, the three sums of an apply 127 -> 50 us).
-template <typename T>
+template <typename T, bool ROWS>
 __global__ __launch_bounds__(256) void k_pair_reduce(PairStream g, int b0, int nb)
 {
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
@@ -898,18 +899,35 @@ __global__ __launch_bounds__(256) void k_pair_reduce(PairStream g, int b0, int n
     const T* St = (const T*)g.stage + (long)b * g.nrows * g.M + r;
     const long k0 = g.tstart[t], k1 = g.tstart[t + 1];
     T sum = T(0);
-    for (long k = k0; k < k1; k += 8) {
-        T v[8];
-        bool in[8];
+    if constexpr (ROWS) {
+        for (long k = k0; k < k1; k += 32) {
+            // the existing ones of 32 rows, then those eight at a time
+            const int n = k1 - k < 32 ? (int)(k1 - k) : 32;
+            unsigned rows = 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            in[u] = k + u < k1;
-            if (g.row_src) in[u] = in[u] && g.row_src[in[u] ? k + u : k0] >= 0;
+            for (int u = 0; u < 32; ++u) rows |= (g.row_src[k + (u < n ? u : 0)] >= 0 && u < n ? 1u : 0u) << u;
+            while (rows) {
+                T v[8];
+                bool in[8];
+                const int first = __builtin_ctz(rows);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    in[u] = rows != 0;
+                    v[u] = St[(k + (rows ? __builtin_ctz(rows) : first)) * g.M];
+                    rows &= rows - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sum += in[u] ? v[u] : T(0);
+            }
         }
+    } else {
+        for (long k = k0; k < k1; k += 8) {
+            T v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = St[(in[u] ? k + u : k0) * g.M];
+            for (int u = 0; u < 8; ++u) v[u] = St[(k + u < k1 ? k + u : k0) * g.M];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) sum += in[u] ? v[u] : T(0);
+            for (int u = 0; u < 8; ++u) sum += k + u < k1 ? v[u] : T(0);
+        }
     }
     T* d = (T*)g.L + (long)(b0 + b) * per + rem;
     *d = g.accumulate ? *d + sum : sum;
@@ -920,7 +938,8 @@ ert_status launch_reduce(hipStream_t s, const PairStream& g, int b0, int nb)
 {
     StageTimer t_(g.prof, s, ERT_STAGE_REDUCE);
     const long n = g.ntarget * g.M * nb;
-    hipLaunchKernelGGL(k_pair_reduce<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, b0, nb);
+    auto kern = g.row_src ? k_pair_reduce<T, true> : k_pair_reduce<T, false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, b0, nb);
     ERT_HIP(hipGetLastError());
     return ERT_OK;
 }
