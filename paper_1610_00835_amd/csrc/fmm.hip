@@ -659,12 +659,15 @@ constexpr int kNearLeaf = 8;                       // cells per leaf side (the p
 constexpr int kNearRow = 24, kNearPlane = 376;     // pitch of a row and a plane of the staged box (16 x 16 x 16 cells)
 constexpr int kNearThreads = 1024, kNearPlanes = 4;
 
-// Offsets d, |d_a| < 2 L, as one index; the list of an offset starts at start[index].
+// Offsets d, |d_a| < 2 L, as one index; the list of an offset starts at start[index].  The plane
+// d2 = 0 comes first, which is all that 2D has.
 __host__ __device__ inline int near_list(int L, int d0, int d1, int d2)
 {
     const int R = 2 * L - 1, side = 4 * L - 1;
-    return (d0 + R) + side * ((d1 + R) + side * (d2 + R));
+    return (d0 + R) + side * ((d1 + R) + side * d2);
 }
+// (offsets that follow zero in the order z, y, x have d2 >= 0)
+inline int near_lists(int D, int L) { return (4 * L - 1) * (4 * L - 1) * (D > 2 ? 2 * L : 1); }
 
 // Cells a ray of offset d can touch: eight at its first sample, at most four more for each
 // cell face it crosses; lists are padded to a multiple of four taps of weight zero.
@@ -685,8 +688,7 @@ __global__ __launch_bounds__(64) void k_near_taps(Geo g, int L, const double* __
     constexpr int B = 2 * kNearLeaf;               // corners -(2 L - 1) .. 0 or 0 .. 2 L - 1 per axis
     __shared__ double acc[B * B * B];
     const int D = g.dim, R = 2 * L - 1, side = 4 * L - 1, li = blockIdx.x, lane = threadIdx.x;
-    const int d[3] = {li % side - R, (li / side) % side - R, D > 2 ? li / (side * side) - R : 0};
-    if (D == 2 && li / (side * side) != R) return;
+    const int d[3] = {li % side - R, (li / side) % side - R, li / (side * side)};
     if (!near_lower(d[0], d[1], d[2])) return;
     const int e0 = abs(d[0]) + 1, e1 = abs(d[1]) + 1, e2 = abs(d[2]) + 1, vol = e0 * e1 * e2;
     const int l0 = d[0] < 0 ? d[0] : 0, l1 = d[1] < 0 ? d[1] : 0, l2 = d[2] < 0 ? d[2] : 0;
@@ -1901,10 +1903,10 @@ ert_status FmmImpl<T>::setup_far_hom(ert_plan_impl* p, int l, double svd_tol)
 ert_status near_blocks(ert_plan_impl* p, const DevTree& dt, HetCache* c, long np)
 {
     hipStream_t s = p->stream;
-    const int L = dt.leaf, side = 4 * L - 1, R = 2 * L - 1;
-    std::vector<NearList> list((size_t)side * side * side, NearList{0.0, 0, 0});
+    const int L = dt.leaf, R = 2 * L - 1;
+    std::vector<NearList> list((size_t)near_lists(dt.D, L), NearList{0.0, 0, 0});
     int total = 0;
-    for (int d2 = dt.D > 2 ? -R : 0; d2 <= (dt.D > 2 ? R : 0); ++d2)
+    for (int d2 = 0; d2 <= (dt.D > 2 ? R : 0); ++d2)
         for (int d1 = -R; d1 <= R; ++d1)
             for (int d0 = -R; d0 <= R; ++d0)
                 if (near_lower(d0, d1, d2)) {
