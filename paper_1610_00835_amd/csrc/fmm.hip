@@ -1894,11 +1894,6 @@ ert_status FmmImpl<T>::setup_far_hom(ert_plan_impl* p, int l, double svd_tol)
     return ERT_OK;
 }
 
-// Heterogeneous far field of level l: the directed interaction-list pairs grouped by
-// target (the staging rows), and one stored matrix per unordered pair {t, s}, t < s,
-// for target t and source s (the transpose serves target s).
-// The corner-octet table of the plan's sigma_t, held while the caches are built
-// (8 doubles per cell); the stream is drained before it is released.
 // The np stored near-field blocks of the cache (k_near_blocks) from freshly formed stencils.
 ert_status near_blocks(ert_plan_impl* p, const DevTree& dt, HetCache* c, long np)
 {
@@ -1935,12 +1930,29 @@ ert_status near_blocks(ert_plan_impl* p, const DevTree& dt, HetCache* c, long np
     return ERT_OK;
 }
 
+// Where a level's translation matrices read sigma_t: staged boxes up to 18 cells a side
+// (k_ops_het_lds), the corner table beyond and in 2D (k_ops_het).
+enum class FarForm { kSmall, kWide, kTable };
+FarForm far_form(const FmmTree& tr, int l)
+{
+    const int wc = tr.leaf << (tr.L - l);
+    if (tr.D == 3 && ops_windows(OpsSmall::SIDE, wc, 3) > 0) return FarForm::kSmall;
+    if (tr.D == 3 && ops_windows(OpsWide::SIDE, wc, 3) > 0) return FarForm::kWide;
+    return FarForm::kTable;
+}
+
+// The corner-octet table of the plan's sigma_t, held while the caches are built
+// (8 doubles per cell); the stream is drained before it is released.  Only for trees
+// with a level that reads it.
 struct CornerTable {
     double* st8 = nullptr;
     hipStream_t s = nullptr;
-    ert_status build(ert_plan_impl* p)
+    ert_status build(ert_plan_impl* p, const FmmTree& tr)
     {
         s = p->stream;
+        bool used = false;
+        for (int l = 2; l <= tr.L; ++l) used = used || far_form(tr, l) == FarForm::kTable;
+        if (!used) return ERT_OK;
         const long n = p->N;
         if (hipMalloc(&st8, std::max<size_t>(1, (size_t)n * 8 * sizeof(double))) != hipSuccess) {
             st8 = nullptr;
@@ -1975,10 +1987,8 @@ ert_status het_fill(ert_plan_impl* p, hipStream_t s, const FmmTree& tr, const do
     const long pchunk = std::max<long>(1, (1L << 27) / KpKp);
     const Geo& g = p->geo;
     const int nl[3] = {tr.nl[l][0], tr.nl[l][1], tr.nl[l][2]};
-    // the boxes and the cells between them in LDS up to 18 cells a side, the corner table beyond
     const int wc = tr.leaf << (tr.L - l);
-    const bool small = tr.D == 3 && ops_windows(OpsSmall::SIDE, wc, 3) > 0;
-    const bool wide = tr.D == 3 && !small && ops_windows(OpsWide::SIDE, wc, 3) > 0;
+    const FarForm form = far_form(tr, l);
     const auto groups = [&](long per) { return (int)(((long)tr.K * tr.K + per - 1) / per); };
     for (long q0 = p0; q0 < p0 + cnt; q0 += pchunk) {
         const long c = std::min(pchunk, p0 + cnt - q0);
@@ -1988,10 +1998,10 @@ ert_status het_fill(ert_plan_impl* p, hipStream_t s, const FmmTree& tr, const do
             hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(threads), 0, s, g, p->d_st, tr.nc, tr.K, tr.Kp,
                                tr.width[l], wc, nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, ngroup, out);
         };
-        if (small) {
+        if (form == FarForm::kSmall) {
             launch(p->o.scheme ? k_ops_het_lds<float, true, OpsSmall> : k_ops_het_lds<float, false, OpsSmall>,
                    OpsSmall::THREADS, OpsSmall::RAYS);
-        } else if (wide) {
+        } else if (form == FarForm::kWide) {
             launch(p->o.scheme ? k_ops_het_lds<float, true, OpsWide> : k_ops_het_lds<float, false, OpsWide>,
                    OpsWide::THREADS, OpsWide::RAYS);
         } else {
@@ -2019,6 +2029,9 @@ ert_status het_gen_fill(const void* ctx, hipStream_t s, long p0, long cnt, float
     return het_fill(c->p, s, *c->tr, c->cheb, c->hc->st8, c->hc, c->l, p0, cnt, dst);
 }
 
+// Heterogeneous far field of level l: the directed interaction-list pairs grouped by
+// target (the staging rows), and one stored matrix per unordered pair {t, s}, t < s,
+// for target t and source s (the transpose serves target s).
 ert_status het_far_level(ert_plan_impl* p, const FmmTree& tr, const double* cheb, const double* st8, HetCache* hc,
                          int l)
 {
@@ -2186,12 +2199,12 @@ ert_status FmmImpl<T>::setup_het(ert_plan_impl* p)
         c->near_fwd = other->near_fwd;
         c->near_bwd = other->near_bwd;
         CornerTable t8;
-        ert_status st = t8.build(p);
+        ert_status st = t8.build(p, tr);
         for (int l = 2; l <= tr.L && st == ERT_OK; ++l) st = het_far_level(p, tr, cheb, t8.st8, c, l);
         if (st != ERT_OK) return fail(st);
         if (c->chunk > 0) {
             c->st8 = t8.release();
-            c->bytes += (size_t)p->N * 8 * sizeof(double);
+            if (c->st8) c->bytes += (size_t)p->N * 8 * sizeof(double);
         }
         if (hipStreamSynchronize(s) != hipSuccess) return fail(ERT_EDEVICE);
         p->het[slot] = c;
@@ -2253,7 +2266,7 @@ ert_status FmmImpl<T>::setup_het(ert_plan_impl* p)
     if (st == ERT_OK) st = upload<long>(s, &c->near_fwd, fwd);
     if (st == ERT_OK) st = upload<long>(s, &c->near_bwd, bwd);
     CornerTable t8;
-    if (st == ERT_OK) st = t8.build(p);
+    if (st == ERT_OK) st = t8.build(p, tr);
     if (st != ERT_OK) return fail(st);
     if (tr.leaf > kNearLeaf) {
         record_error("FMM: leaf larger than the near-field block kernel supports");
@@ -2265,7 +2278,7 @@ ert_status FmmImpl<T>::setup_het(ert_plan_impl* p)
     if (st != ERT_OK) return fail(st);
     if (c->chunk > 0) {
         c->st8 = t8.release();
-        c->bytes += (size_t)p->N * 8 * sizeof(double);
+        if (c->st8) c->bytes += (size_t)p->N * 8 * sizeof(double);
     }
     p->het[slot] = c;
     hc = c;

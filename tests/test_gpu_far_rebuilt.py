@@ -79,3 +79,26 @@ def test_all_levels_rebuilt_mixed_solve(ev):
     assert ib["rel_resid_true"] <= 1e-8
     assert np.array_equal(Ub, Ua)
     assert np.array_equal(yb, ya)
+
+
+@pytest.mark.parametrize("n,leaf,table", [((16, 16, 16), 4, False), ((50, 37), 8, True), ((140, 9, 5), 8, True)])
+def test_corner_table_kept_where_it_is_read(ev, n, leaf, table):
+    """Budget of nothing: beside the near blocks a plan keeps one block of scratch, and the corner
+    table (64 bytes per cell) only when a level reads it (2D, boxes past 18 cells a side); the
+    results are the stored plan's."""
+    N = int(np.prod(n))
+    st = np.random.default_rng(3).uniform(1.0, 5.0, N)
+    x = _vectors(N, 1, 31)
+    kw = dict(kernel=1, method="fmm", prec="fp64", leaf=leaf, cheb_n=4)
+    with ev.Plan(len(n), n, 1.0 / 64, st, 0.9 * st, **kw) as a:
+        ia = a.fmm_info()
+        ya = gpu_apply(a, x, ev.OP_A)
+    with ev.Plan(len(n), n, 1.0 / 64, st, 0.9 * st, far_cache_gb=1e-12, **kw) as b:
+        ib = b.fmm_info()
+        ys = [gpu_apply(b, x, ev.OP_A) for _ in range(3)]
+    block = ia["nodes_padded"] ** 2 * 4
+    near = ia["cache_bytes"] - sum(ia["far_pairs"]) // 2 * block
+    assert any(ib["far_rebuilt"])
+    assert 0 <= ib["cache_bytes"] - near - (64 * N if table else 0) <= block
+    for y in ys:
+        assert np.array_equal(y, ya)
