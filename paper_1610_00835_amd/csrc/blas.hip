@@ -183,7 +183,7 @@ __global__ void k_zero(double* __restrict__ y, long N)
     if (i < N) y[i] = 0.0;
 }
 
-// workgroups of a reduction: at least 64 values each, at most kRedBlocks
+// workgroups of a reduction: about 64 values each at least, at most kRedBlocks
 inline int red_blocks(long N)
 {
     int nb = kRedBlocks;

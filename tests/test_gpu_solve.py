@@ -298,3 +298,22 @@ def test_gram_schmidt_sizes(n):
     assert info["converged"] == 1 and info["restarts"] == 0
     assert abs(info["rel_resid_est"] - info["rel_resid_true"]) <= 1e-13
     assert info["iters"] > 8 or N < 64
+
+
+def test_gram_schmidt_past_1024_columns():
+    """Optically thick cells make I - K diagonal, 1 - albedo per cell; with 3600 values of it
+    spread over five decades GMRES to 1e-8 takes about 1400 steps (1385 in exact bookkeeping on
+    the host), so a step subtracts the basis in two passes.  Estimate and true residual: the
+    iterate is up to 1e5 times the right-hand side, 2^-53 1e5 sqrt(1400) = 4e-10 of rounding."""
+    import torch
+    from paper_1610_00835_amd import ertvie
+    N, sigma = 3600, 800.0
+    rng = np.random.default_rng(0)
+    ss = sigma * (1.0 - 10.0 ** (-5.0 * rng.uniform(0.0, 1.0, N)))
+    phi = torch.from_numpy(rng.uniform(0.5, 1.5, N)).cuda()
+    U = torch.empty_like(phi)
+    with ertvie.Plan(2, (60, 60), 1.0, np.full(N, sigma), ss, method="direct", prec="fp64") as plan:
+        info = plan.solve(phi, U, tol=1e-8, max_iter=1600, rhs_is_phi=True)
+    assert info["converged"] == 1 and info["restarts"] == 0
+    assert info["iters"] > 1100
+    assert abs(info["rel_resid_est"] - info["rel_resid_true"]) <= 1e-9

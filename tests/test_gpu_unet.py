@@ -388,3 +388,72 @@ def test_channel_counts_are_refused_at_every_size(ev, n, B, widths, forward):
         with pytest.raises(ev.ErtError) as x:
             net.grad(_dev(r), _dev(e), _dev(st), _dev(ss))
         assert x.value.status == ev.EUNSUPPORTED
+
+
+def _separated(seed, widths, xs):
+    """Ordinary weights, with biases that keep every unit a tenth of its channel's range away from
+    zero on the samples xs (half of the channels active, half not): activations vary from voxel
+    to voxel and no mask can differ from the reference's.  Returns the flat parameters."""
+    layers = U.unpack(_params(seed, widths).astype(np.float64), widths)
+    rng = np.random.default_rng(seed + 2)
+
+    def block(inp, li):
+        W, b = layers[li]
+        pre = [U.conv3(U.bf16_split(x), U.bf16_round(W), np.zeros(W.shape[0])) for x in inp]
+        lo = np.min([p.min(axis=(1, 2, 3)) for p in pre], axis=0)
+        hi = np.max([p.max(axis=(1, 2, 3)) for p in pre], axis=0)
+        on = rng.permutation(W.shape[0]) < W.shape[0] // 2
+        b[...] = np.where(on, -lo + 0.1 * (hi - lo), -hi - 0.1 * (hi - lo)).astype(np.float32)
+        return [np.maximum(p + b[:, None, None, None], 0.0) for p in pre]
+
+    def join(a, b):
+        return [np.concatenate([U.up2(p), q]) for p, q in zip(a, b)]
+
+    s1 = block(block(xs, 0), 1)
+    s2 = block(block([U.pool2(x) for x in s1], 2), 3)
+    e3 = block(block([U.pool2(x) for x in s2], 4), 5)
+    d2 = block(block(join(e3, s2), 6), 7)
+    d1 = block(block(join(d2, s1), 8), 9)
+    W, b = layers[10]                                # outputs of mean zero and size one
+    y = np.concatenate([np.einsum("i,izyx->zyx", W[0, :, 0, 0, 0], x).ravel() for x in d1])
+    W /= y.std()
+    b[...] = -y.mean() / y.std()
+    return U.pack(layers).astype(np.float32)
+
+
+# full level in tiles of 128 voxels (VT 2) forward and backward; half level in whole-layer tiles of
+# 64 (eight columns of 32^3; the reference takes the first and the last); coarse levels split
+@pytest.mark.parametrize("n,B,cols,grad", [((44, 36, 24), 2, (0, 1), True), ((32, 32, 32), 8, (0, 7), False),
+                                           ((12, 20, 28), 1, (0,), True)])
+def test_structured_activations_match_reference(ev, n, B, cols, grad):
+    """As test_tiled_layers_match_reference, with activations that vary by their whole size over
+    a grid: a pair of voxels swapped in one layer, the low part of the split activations left
+    out or a mask left out moves the output or a gradient past the bars."""
+    import torch
+    r, e, st, ss = _rand(n, B, 14)
+    X, S = _oracle_inputs(r[list(cols)], st[list(cols)], ss[list(cols)], n)
+    p = _separated(15, WIDTHS, list(X))
+    with ev.Net(n, batch_max=B) as net:
+        net.set_params(p)
+        z = torch.empty((B, int(np.prod(n))), dtype=torch.float64, device="cuda")
+        net.forward(_dev(r), _dev(st), _dev(ss), z)
+        zg = _host(z)[list(cols)]
+        loss, g = net.grad(_dev(r), _dev(e), _dev(st), _dev(ss)) if grad else (None, None)
+    Y = U.forward(p.astype(np.float64), X, WIDTHS, bf16=True)
+    err = rel_l2(zg - r[list(cols)], Y.reshape(len(cols), -1) * S[:, None])
+    log("unet forward", n, B, "rel L2", err)
+    assert err <= 1e-4
+    if not grad:
+        return
+    T = np.stack([U.target(r[b], e[b]).astype(np.float32).astype(np.float64).reshape(n[2], n[1], n[0])
+                  for b in range(B)])
+    Lr, gr = U.loss_and_grad(p.astype(np.float64), X, T, WIDTHS, bf16=True)
+    assert abs(loss - Lr) <= 1e-4 * abs(Lr)
+    o = 0
+    for li, (co, ci, k) in enumerate(U.layer_shapes(WIDTHS)):
+        nw = co * ci * k ** 3
+        for name, a, b in (("W", o, o + nw), ("b", o + nw, o + nw + co)):
+            err = rel_l2(g[a:b].astype(np.float64), gr[a:b])
+            log("  layer", li + 1, name, "rel L2", err)
+            assert err <= 1e-3, (li + 1, name, err)
+        o += nw + co
