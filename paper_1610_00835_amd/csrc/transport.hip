@@ -66,25 +66,6 @@ __device__ __forceinline__ double phi1_one(const Phi1& f, double x)
 // exp(-x) - 1; a call, so that its constants don't sit in registers through the march
 __device__ __noinline__ double thick_step(double x) { return expm1(-x); }
 
-// Steps of the ray from cell c backwards along -v to the box boundary, and their length.
-template <int DIM>
-__device__ __forceinline__ void ray_steps(double h, const int (&n)[3], const int (&c)[DIM], const double (&v)[DIM], int* m,
-                                          double* D)
-{
-    double sb = 1e300;
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        const double x = h * (c[a] + 0.5);
-        if (v[a] > 0.0) sb = fmin(sb, x / v[a]);
-        else if (v[a] < 0.0) sb = fmin(sb, (n[a] * h - x) / (-v[a]));
-    }
-    // the relative margin keeps the count of an exact multiple of h/2 (every
-    // axis-parallel ray) independent of the last bit of sb
-    const double q0 = ceil(sb / (0.5 * h) * (1.0 - 1e-12));
-    *m = q0 < 1.0 ? 1 : (int)q0;
-    *D = sb / (double)*m;
-}
-
 // One step of length D in (sigma_t, Q) = s: att = exp(-tau) before the step.
 __device__ __forceinline__ void ray_step(const Phi1& coef, double2 s, double D, double& acc, double& att)
 {
@@ -142,11 +123,10 @@ SweepTile sweep_tile(const Geo& g)
 // between distances w W and (w + 1) W (in cells) are a box, staged in LDS before the window, cells
 // outside the grid with the value of the face (the clamped rule).  In cells the sample q = 1/2,
 // 3/2, .. of cell i sits at i - q e per axis (cell centres are whole numbers); the box allows it
-// a rounding of kSlack.  W is the largest whose box fits for this direction, at most 16 cells and
-// the longest ray of the tile.
+// a rounding of kSlack.  W is the largest whose box fits for this direction, 16 cells at most.
 // Bound: FP64 arithmetic (75 instructions per step; a hundred and fifty with clamps, expm1 and a
 // division), then LDS reads (eight corners of 16 bytes; as gathers through L1 at half the rate
-// they were the bound).  64^3 x 26 directions: 2.46 -> 1.52 ms; 512^2 x 26: 12.5 -> 5.8 ms.
+// they were the bound).  64^3 x 26 directions: 2.46 -> 1.53 ms; 512^2 x 26: 12.5 -> 5.8 ms.
 template <int DIM>
 __global__ __launch_bounds__(kSweepThreads, 6) void k_sweep(Geo g, SweepTile tile, Phi1 coef,
                                                             const double2* __restrict__ sq,
@@ -174,21 +154,25 @@ __global__ __launch_bounds__(kSweepThreads, 6) void k_sweep(Geo g, SweepTile til
         }
         in = in && t == 0;
     }
-    int m;
-    double D;
-    ray_steps<DIM>(h, n, c, v, &m, &D);
-    if (!in) m = 0, D = h;
-    const double per_cell = h / D;   // steps per cell length
-    double e[DIM], longest = 16.0;   // longest: no ray of the tile is longer (cells)
+    // distance backwards along -v to the box boundary
+    double sb = 1e300;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        const int last = lo[a] + (1 << tile.s[a]) - 1, top = last < n[a] - 1 ? last : n[a] - 1;
-        if (v[a] > 0.0) longest = fmin(longest, (top + 0.5) / v[a]);
-        else if (v[a] < 0.0) longest = fmin(longest, (n[a] - lo[a] - 0.5) / -v[a]);
-        e[a] = -D * v[a] / h;
+        const double x = h * (c[a] + 0.5);
+        if (v[a] > 0.0) sb = fmin(sb, x / v[a]);
+        else if (v[a] < 0.0) sb = fmin(sb, (n[a] * h - x) / (-v[a]));
     }
+    // the relative margin keeps the count of an exact multiple of h/2 (every
+    // axis-parallel ray) independent of the last bit of sb
+    const double q0 = ceil(sb / (0.5 * h) * (1.0 - 1e-12));
+    const int m = !in ? 0 : q0 < 1.0 ? 1 : (int)q0;
+    const double D = in ? sb / (double)m : h;
+    const double per_cell = h / D;   // steps per cell length
+    double e[DIM];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) e[a] = -D * v[a] / h;
     // the window
-    int W = (int)ceil(longest);
+    int W = 16;
     for (; W > 1; --W) {
         int vol = 1;
 #pragma unroll
@@ -283,9 +267,17 @@ __global__ __launch_bounds__(256) void k_sweep_thin(Geo g, Phi1 coef, const doub
         rest /= n[a];
         v[a] = dirs[DIM * d + a];
     }
-    int m;
-    double D;
-    ray_steps<DIM>(h, n, c, v, &m, &D);
+    // the ray and its steps as in k_sweep (one function for both took 3 more registers to memory there)
+    double sb = 1e300;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const double x = h * (c[a] + 0.5);
+        if (v[a] > 0.0) sb = fmin(sb, x / v[a]);
+        else if (v[a] < 0.0) sb = fmin(sb, (n[a] * h - x) / (-v[a]));
+    }
+    const double q0 = ceil(sb / (0.5 * h) * (1.0 - 1e-12));
+    const int m = q0 < 1.0 ? 1 : (int)q0;
+    const double D = sb / (double)m;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) e[a] = -D * v[a] / h;
     double acc = 0.0, att = 1.0, q = 0.5;
