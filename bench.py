@@ -594,8 +594,8 @@ def transport_s3(torch, inputs, plan, fd, U0, N):
         steps += int(np.maximum(1, np.ceil(sb / (0.5 / n) * (1 - 1e-12))).sum())
     out = {"directions": len(dirs), "seconds": ts, "cell_directions_per_s": N * len(dirs) / ts,
            "ray_steps": steps, "steps_per_s": steps / ts,
-           # eight interpolation corners of one (sigma_t, Q) pair, 16 bytes each
-           "l2_gather_bytes_per_s": steps * 8 * 16 / ts}
+           # eight interpolation corners of one (sigma_t, Q) pair, 16 bytes each, from boxes in LDS
+           "lds_read_bytes_per_s": steps * 8 * 16 / ts}
     log("128^3 S.3:", json.dumps(out))
     return out
 

@@ -369,7 +369,9 @@ typedef struct {
     int cheb_n;           /* Chebyshev nodes per axis */
     int nodes;            /* nodes per box (cheb_n^dim) */
     int nodes_padded;     /* nodes per box as stored (multiple of 32) */
-    int rank[16];         /* per level: compressed translation rank as stored, 0 = uncompressed */
+    int rank[16];         /* per level: compressed translation rank as stored, 0 = uncompressed (FP64
+                             2D homogeneous plans with 8-cell leaves store the compressed map
+                             as full matrices and have form_near, form_far -1) */
     long far_pairs[16];   /* per level: (target, source) box pairs of the interaction lists */
     long near_pairs;      /* point pairs of the near field (self pairs excluded) */
     int form_near;        /* execution form of the homogeneous near-field product for one
@@ -474,7 +476,9 @@ typedef struct {
     int dim;          /* 3 */
     int n[3];         /* cells per axis, each a positive multiple of 4 */
     int batch_max;    /* largest batch of forward/grad/train calls; 0 -> 1 */
-    int width[3];     /* channel widths w1, w2, w3; 0 -> 16, 32, 64; multiples of 16, <= 128 */
+    int width[3];     /* channel widths w1, w2, w3; 0 -> 16, 32, 64; multiples of 16, <= 128; a
+                         layer's output count must be 16, 32, 48, 64, 96 or 128 (forward: w1, w2, w3;
+                         gradients also w3 + w2 and w2 + w1), others are ERT_EUNSUPPORTED when run */
     int reserved[4];  /* must be 0 */
 } ert_net_opts;
 

@@ -22,11 +22,11 @@
 //  - 2D levels above it take one launch down (both pre-sweeps, residual and
 //    restriction) and one up (prolongation and both post-sweeps) over LDS tiles with
 //    a halo as wide as the half-sweeps reach (k_tile), instead of five and five.
-//    With both, a 2D 264^2 solve of 10 steps takes 4.40 ms instead of 10.7.
+//    With both, a 2D 264^2 solve of 10 steps takes 2.05 ms instead of 10.7.
 //  - In 3D such tiles would be mostly halo (an 8^3 tile of an 18^3 box), so the
 //    larger levels keep one launch per half-sweep.
 // Face coefficients are stored divided by h^2 and the smoother multiplies by the
-// inverse diagonal.
+// inverse diagonal.  Cells and threads are 32-bit: a plan has at most 2^30 cells.
 #include "common.hpp"
 
 #include <algorithm>
@@ -220,7 +220,7 @@ __global__ void k_prolong_add(int f0, int f1, int f2, double* __restrict__ Uf, i
 // Neighbouring tiles read each other's U_in, so U_out is another buffer.
 // Bound: launch latency, the load of a cell's nine values and the four barriers.  Tiles of 16
 // cells, one cell of the box per thread, spread a level over the chip: 264^2, 66 us per
-// application (20 launches); 86 us with tiles of 32 and two cells per thread, 150 us with
+// application (18 launches); 86 us with tiles of 32 and two cells per thread, 150 us with
 // seven.  The larger tile pays where a level has more of them than the chip holds at once
 // (2048^2: 414 against 562 us): its halo doubles a cell's traffic instead of tripling it.
 constexpr int kHalo = 5;

@@ -12,7 +12,7 @@
 //            nothing but the up pass, in one launch on the matrix cores;
 //   down     two levels of L2L per launch; the last one goes on to L2P, adds the near
 //            field and assembles y.
-// 512^2 (order 6): 5 launches, 231 -> 64 us; 64^2 (order 8): 3 launches, 78 -> 28 us; 2048^2
+// 512^2 (order 6): 5 launches, 231 -> 63 us; 64^2 (order 8): 3 launches, 78 -> 30 us; 2048^2
 // (order 8) 1380 -> 1180 us, now bound by the FP64 matrix pipe (24 GFLOP).  64 right-hand
 // sides: 64^2 147 -> 133 us, 512^2 (order 6) 3.65 -> 1.88 ms.
 //

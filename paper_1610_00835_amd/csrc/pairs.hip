@@ -885,7 +885,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // contiguous directed rows in order, skipping rows of pairs that do not exist (ROWS: marked
 // in row_src; near fields of thin grids have as few as 3 of 27).
 // Bound: the staging rows' traffic; eight rows are in flight per thread (one at a time,
-// behind its index: 48^3, order 6, the three sums of an apply 127 -> 50 us).
+// behind its index: 48^3, order 6, the three sums of an apply 127 -> 38 us).
 template <typename T, bool ROWS>
 __global__ __launch_bounds__(256) void k_pair_reduce(PairStream g, int b0, int nb)
 {
