@@ -64,3 +64,19 @@ def test_stage_profile(n):
             assert np.array_equal(gpu_apply(plan, x, ertvie.OP_A), want)
     stages = {"near", "p2m", "m2l", "l2p"} | ({"m2m", "l2l"} if levels > 2 else set())
     assert {k for k, v in prof.items() if v[0] > 0.0 and v[1] > 0} == stages
+
+
+@pytest.mark.parametrize("n,order", [((260, 133), 5), ((264, 264), 8)])
+def test_hom2d_second_kernel_on_larger_trees(n, order):
+    """The kernel of cell integrals (scheme 1) on trees of five and six levels; same bar."""
+    from paper_1610_00835_amd import ertvie
+    N = n[0] * n[1]
+    ss = np.random.default_rng(7).uniform(0.0, 3.0, N)
+    X = inputs.random_vector(N, 3, nrhs=3)
+    kw = dict(method="fmm", prec="fp64", cheb_n=order, nrhs_max=3, scheme=1)
+    with ertvie.Plan(2, n, 1.0 / max(n), np.full(N, 3.0), ss, form=(1, 1), **kw) as a, \
+            ertvie.Plan(2, n, 1.0 / max(n), np.full(N, 3.0), ss, **kw) as b:
+        assert b.fmm_info()["form_near"] == -1
+        for op in (ertvie.OP_G, ertvie.OP_A):
+            ya, yb = gpu_apply(a, X, op), gpu_apply(b, X, op)
+            assert max(rel_l2(yb[:, k], ya[:, k]) for k in range(3)) <= 1e-12
