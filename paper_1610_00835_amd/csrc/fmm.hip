@@ -1039,6 +1039,13 @@ struct OpsForm {
 };
 using OpsSmall = OpsForm<21, 460, 512, 8>;
 using OpsWide = OpsForm<27, 744, 1024, 4>;
+// Launches that leave CUs with fewer than two workgroups (small trees, rebuilt levels with room
+// for a few blocks) take one ray per thread and eight (four) times the workgroups: a block of
+// 216 nodes is then 92 workgroups instead of 12 (40 x 32 x 32, every block rebuilt by itself:
+// an apply 274 -> 99 ms; the former kernel's 46 workgroups of two rays 136).
+using OpsSmallFew = OpsForm<21, 460, 512, 1>;
+using OpsWideFew = OpsForm<27, 744, 1024, 1>;
+constexpr long kOpsFew = 512;
 
 // Windows of a pair of boxes of wc cells a side, omax boxes apart: the fewest whose staged
 // boxes of `side` cells fit; 0 when none up to 32 do or a ray may have too many steps
@@ -1993,17 +2000,19 @@ ert_status het_fill(ert_plan_impl* p, hipStream_t s, const FmmTree& tr, const do
     for (long q0 = p0; q0 < p0 + cnt; q0 += pchunk) {
         const long c = std::min(pchunk, p0 + cnt - q0);
         float* out = dst + (size_t)(q0 - p0) * KpKp;
-        auto launch = [&](auto kern, int threads, int rays) {
-            const int ngroup = groups((long)threads * rays);
-            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(threads), 0, s, g, p->d_st, tr.nc, tr.K, tr.Kp,
+        auto launch = [&](auto f) {
+            using F = decltype(f);
+            const int ngroup = groups((long)F::THREADS * F::RAYS);
+            auto kern = p->o.scheme ? k_ops_het_lds<float, true, F> : k_ops_het_lds<float, false, F>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(c * ngroup)), dim3(F::THREADS), 0, s, g, p->d_st, tr.nc, tr.K, tr.Kp,
                                tr.width[l], wc, nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, ngroup, out);
         };
         if (form == FarForm::kSmall) {
-            launch(p->o.scheme ? k_ops_het_lds<float, true, OpsSmall> : k_ops_het_lds<float, false, OpsSmall>,
-                   OpsSmall::THREADS, OpsSmall::RAYS);
+            if (c * groups((long)OpsSmall::THREADS * OpsSmall::RAYS) < kOpsFew) launch(OpsSmallFew{});
+            else launch(OpsSmall{});
         } else if (form == FarForm::kWide) {
-            launch(p->o.scheme ? k_ops_het_lds<float, true, OpsWide> : k_ops_het_lds<float, false, OpsWide>,
-                   OpsWide::THREADS, OpsWide::RAYS);
+            if (c * groups((long)OpsWide::THREADS * OpsWide::RAYS) < kOpsFew) launch(OpsWideFew{});
+            else launch(OpsWide{});
         } else {
             hipLaunchKernelGGL(k_ops_het<float>, dim3(blocks(c * KpKp)), dim3(kB), 0, s, g, st8, tr.D, tr.nc, tr.K,
                                tr.Kp, tr.width[l], nl[0], nl[1], nl[2], cheb, hc->hua[l], hc->hub[l], q0, c, out,

@@ -102,3 +102,21 @@ def test_corner_table_kept_where_it_is_read(ev, n, leaf, table):
     assert 0 <= ib["cache_bytes"] - near - (64 * N if table else 0) <= block
     for y in ys:
         assert np.array_equal(y, ya)
+
+
+def test_blocks_made_one_by_one(ev):
+    """40 x 40 x 24, order 6: the stored plan makes the 8-cell and the 16-cell boxes' blocks in
+    launches that fill the chip, the plan without a budget one block per launch with another split
+    of its rays over the threads; the values are the same bits."""
+    n = (40, 40, 24)
+    N = int(np.prod(n))
+    st = np.random.default_rng(3).uniform(1.0, 5.0, N)
+    x = _vectors(N, 1, 31)
+    kw = dict(kernel=1, method="fmm", prec="fp64", leaf=8, cheb_n=6)
+    with ev.Plan(3, n, 1.0 / 64, st, 0.9 * st, **kw) as a:
+        ia = a.fmm_info()
+        ya = gpu_apply(a, x, ev.OP_A)
+    assert ia["levels"] == 3 and min(ia["far_pairs"][2:]) // 2 * 12 >= 512
+    with ev.Plan(3, n, 1.0 / 64, st, 0.9 * st, far_cache_gb=1e-12, **kw) as b:
+        assert b.fmm_info()["far_rebuilt"] == [0, 0, 1, 1]
+        assert np.array_equal(gpu_apply(b, x, ev.OP_A), ya)
