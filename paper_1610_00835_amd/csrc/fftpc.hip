@@ -63,7 +63,8 @@ constexpr int kMaxPeriod = 1024;
 // 96^3 (periods of 192): 16 lines in 60 KB 152 us, 8 lines 111 us; 100 x 264: 31 and 23 us.
 // Across the axis four lines (32 contiguous bytes) are kept up to the whole 64 KB while they
 // give two workgroups per CU: 192^3 872 us with two lines, 670 with four; 256^3 2180 and 1583.
-// 264^2 has too few: four lines 36 us, one 29.
+// 264^2 has too few: four lines 36 us, one 29.  In 3D fewer than four lines across it gain
+// nothing for the small grids either (24^3: four 27.0 us, one 28.0; 2D 128^2: 20.6 and 18.9).
 constexpr size_t kLdsWant = 32 * 1024;
 constexpr long kMinGroups = 512;
 
@@ -443,7 +444,7 @@ ert_status launch_lines(hipStream_t s, Lines L, const void* src, void* dst, cons
     L.LTX = 4;
     while (L.LTX > 0 && lds_bytes<R>(L.m, 1 << L.LTX, along) >
                             (!along && L.LTX == 2 && groups(2) >= kMinGroups ? kLdsMax : kLdsWant)) --L.LTX;
-    while (L.LTX > 0 && groups(L.LTX) < kMinGroups) --L.LTX;
+    while (L.LTX > (along || L.B == 1 ? 0 : 2) && groups(L.LTX) < kMinGroups) --L.LTX;
     const size_t lds = lds_bytes<R>(L.m, 1 << L.LTX, along);
     if (lds > kLdsMax) {
         record_error("ert_vie_fft_precond: line transform does not fit in LDS");
